@@ -225,6 +225,66 @@ __device__ __forceinline__ void plan_cheb_lanes(const PropParams& p, double nu, 
     s_out = (key >> 6) & 63;
 }
 
+// Sum over the 16 lanes of each row, FP32.
+__device__ __forceinline__ float row16_sum_f(float x) {
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xF, 0xF, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xF, 0xF, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xF, 0xF, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xF, 0xF, false));
+    return x;
+}
+
+// Sum over the wave's lanes; the same value in every lane (rounding upward is
+// the caller's).
+__device__ __forceinline__ float wave_sum_f(float x) {
+    x = row16_sum_f(x);
+    const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 0));
+    const float b = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16));
+    const float c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 32));
+    const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 48));
+    return (a + b) + (c + d);
+}
+
+// Upper bound of ||G_j||_2 <= sum_m |w_m| ||B_m||_2 from the lanes' weights
+// (lane m holds weight m and beta_m, zero past the basis).  The 1-norm of the
+// formed exponent, the planner's bound before, is larger for a dense G (by
+// up to sqrt(d): 4 times on 64-level GUE systems) and costs a matrix of
+// square roots, row sums and, on several waves, barriers.
+__device__ __forceinline__ double spectral_bound(double w, float beta) {
+    return (double)(wave_sum_f(fabsf((float)w) * beta) * (1.0f + 0x1p-18f));
+}
+
+__device__ __forceinline__ float lane_beta_of(const PropParams& p, int m) { return m < p.M ? p.beta[m] : 0.0f; }
+
+__device__ __forceinline__ double lane_sth_of(const PropParams& p, int lane) {
+    return lane < kSchemes ? p.sth[lane] : -1.0;
+}
+
+// The cheapest evaluation scheme whose threshold covers the bound, without
+// squarings; -1 if there is none (one comparison and a bit scan).
+__device__ __forceinline__ int plan_scheme(double bound, double lane_sth) {
+    const unsigned long long ok = __ballot(bound <= lane_sth);
+    return ok ? __builtin_ctzll(ok) : -1;
+}
+
+// Scheme and squarings: the fewest products plus squarings, ties to the
+// fewer squarings; with force_s >= 0 the smallest scheme that suffices after
+// them (the largest if none does).
+__device__ __forceinline__ void plan_scheme_s(const PropParams& p, double bound, int lane, double lane_sth, int& q,
+                                              int& s) {
+    if (p.force_s >= 0) {
+        q = plan_scheme(ldexp(bound, -p.force_s), lane_sth);
+        if (q < 0) q = p.qmax;
+        s = p.force_s;
+        return;
+    }
+    const int sl = min(min_squarings(bound, lane_sth > 0.0 ? lane_sth : 1.0), 62);
+    int key = lane_sth > 0.0 ? ((lane + sl) << 12) | (sl << 5) | lane : 0x7fffffff;
+    key = __builtin_amdgcn_readfirstlane(row16_min_i(key));
+    q = key & 31;
+    s = (key >> 5) & 127;
+}
+
 // Branch-free form of slice_weight for a lane-dependent basis index m: the
 // lane gathers up to five samples of the slice and combines them with the
 // formula of its basis matrix.  Lanes m >= M get weight 0.
@@ -355,6 +415,19 @@ __device__ __forceinline__ double m6_weight(const PropParams& p, const WeightRec
     return r.kind == 5 ? 0.0 : w;
 }
 
+// Upper bound of the sixth-order exponent's 2-norm from the moments'
+// bounds p_i = sum |w| beta (lane 16 q + m holds a weight of moment q + 1):
+// ||R1|| <= 2 p1 p2, ||R2|| <= (1/30) p1 (2 p3 + r1), and the outer commutator.
+__device__ __forceinline__ double m6_bound(double w, float beta) {
+    const float t = row16_sum_f(fabsf((float)w) * beta);
+    const float p1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 0));
+    const float p2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 16));
+    const float p3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 32));
+    const float r1 = 2.0f * p1 * p2, r2 = p1 * (2.0f * p3 + r1) * (1.0f / 30.0f);
+    return (double)((p1 + p3 * (1.0f / 12.0f) + (20.0f * p1 + p3 + r1) * (p2 + r2) * (1.0f / 120.0f)) *
+                    (1.0f + 0x1p-16f));
+}
+
 // DPP row rotation (within each row of 16 lanes) of a double.
 template <int CTRL>
 __device__ __forceinline__ double dpp_d(double x) {
@@ -394,14 +467,6 @@ __device__ __forceinline__ double rows_max(double x) {
 // and returns it in FP64.
 __device__ __forceinline__ float abs_bound_f(double re, double im) {
     return __builtin_amdgcn_sqrtf((float)(re * re + im * im));
-}
-
-__device__ __forceinline__ float row16_sum_f(float x) {
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xF, 0xF, false));
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xF, 0xF, false));
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xF, 0xF, false));
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xF, 0xF, false));
-    return x;
 }
 
 __device__ __forceinline__ double rows_max_f(float x) {

@@ -294,7 +294,7 @@ __device__ Tile<double> chain_checkpoint(const PropParams& p, int64_t chain, con
     Tile<double> P = ident<double>(L);
     // leaves [0, b) as aligned tree nodes, earliest first: at level l the
     // first d_l nodes of b's group, d_l the base-kFanIn digit l of b
-    const int64_t b = chain / G::NT;
+    const int64_t b = chain / p.chains_per_leaf;
     int nlev = 0;
     for (int64_t cnt = p.n_leaves; cnt > 1; cnt = (cnt + kFanIn - 1) / kFanIn) ++nlev;
     for (int l = nlev; l >= 0; --l) {
@@ -320,7 +320,7 @@ __device__ Tile<double> chain_checkpoint(const PropParams& p, int64_t chain, con
                 P = mul2<G>(node_load<G>(p.nodes + (off + first + k) * NN, L), P, L, s0, s1);
         }
     }
-    for (int64_t c = b * G::NT; c < chain; ++c)
+    for (int64_t c = b * p.chains_per_leaf; c < chain; ++c)
         P = mul2<G>(node_load<G>(p.chain_out + c * NN, L), P, L, s0, s1);
     return P;
 }
@@ -962,7 +962,8 @@ hipError_t launch_traj(const TrajParams& tp, size_t lds, hipStream_t stream) {
 
 }  // namespace
 
-int mfma_chains_per_block(int D);
+// One-wave teams per block of the 16-wide kernels; a larger team is a block.
+constexpr int mfma_chains_per_block(int D) { return D == 16 ? 4 : 1; }
 
 hipError_t launch_trajectory(int D, const TrajParams& tp, hipStream_t stream) {
     const int NT = mfma_chains_per_block(D);

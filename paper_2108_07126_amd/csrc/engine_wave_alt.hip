@@ -1,0 +1,25 @@
+// One-wave teams: the sixth-order scheme and the Chebyshev series.
+#include "wave_kernel.h"
+
+namespace pm {
+
+hipError_t launch_wave_m6(int D, const PropParams& p, hipStream_t stream) {
+    const bool ch = p.method == PM_EXPM_CHEBYSHEV;
+    if (D == 16) {
+        if (ch) return launch_wave_one<1, 4, EXPO_M6, true, false, true>(p, stream);
+        return p.du <= 8 ? launch_wave_one<1, 2, EXPO_M6, false, false, true>(p, stream)
+                         : launch_wave_one<1, 4, EXPO_M6, false, false, true>(p, stream);
+    }
+    if (ch) return launch_wave_one<2, 8, EXPO_M6, true, false, false>(p, stream);
+    if (wave_lds_bytes<2>(p.K + 1, true) > 160 * 1024)
+        return launch_wave_one<2, 8, EXPO_M6, false, false, false>(p, stream);
+    return launch_wave_one<2, 8, EXPO_M6, false, false, true>(p, stream);
+}
+
+hipError_t launch_wave_cheb(int D, const PropParams& p, hipStream_t stream) {
+    if (D == 32) return launch_wave_one<2, 8, EXPO_BASIS, true, false, false>(p, stream);
+    return p.M <= 16 ? launch_wave_one<1, 4, EXPO_BASIS, true, false, true>(p, stream)
+                     : launch_wave_one<1, 4, EXPO_BASIS, true, false, false>(p, stream);
+}
+
+}  // namespace pm

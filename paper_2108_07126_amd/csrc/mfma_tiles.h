@@ -515,13 +515,13 @@ __device__ __forceinline__ Tile<double> reg_mul_stk(const double (&ar)[4], const
 
 // Zero the off-diagonal 8 x 8 blocks of a slice-pair tile (FP64 layout:
 // register r holds row g + 4r, in the second block for r >= 2).
-__device__ __forceinline__ void pair_mask(Tile<double>& t, const Lane& L) {
+__device__ __forceinline__ void pair_mask(Tile<double>& t, int col) {
     // unconditional selects: conditional stores into the tile's registers can
     // be merged into a store through a chosen address, which keeps the tile
     // in scratch memory
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const bool cross = (r >= 2) != (L.j >= 8);
+        const bool cross = (r >= 2) != (col >= 8);
         t.re[r] = cross ? 0.0 : t.re[r];
         t.im[r] = cross ? 0.0 : t.im[r];
     }
@@ -881,163 +881,6 @@ __device__ __forceinline__ Tile<double> node_load(const double* node, const Lane
         t.im[r] = node[(row * G::D + col) * 2 + 1];
     }
     return t;
-}
-
-// Z - Z^H for a tile set Z (FP64): the adjoint is read back transposed from
-// an LDS slot.  For Hermitian X and Y, (XY)^H = YX, so the commutator
-// [X, Y] is XY - (XY)^H: one product instead of two.
-template <class G>
-__device__ __forceinline__ Tile<double> minus_adjoint(const Tile<double>& Z, const Lane& L, double* slot) {
-    team_sync<G>();
-    slot_store<G, double>(slot, Z, L);
-    team_sync<G>();
-    const double* re = slot;
-    const double* im = slot + G::PLANE;
-    const int col = 16 * L.TJ + L.j;
-    Tile<double> o;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int row = 16 * L.TI + crow<double>(L.g, r);
-        o.re[r] = Z.re[r] - re[col * G::LD + row];
-        o.im[r] = Z.im[r] + im[col * G::LD + row];
-    }
-    return o;
-}
-
-// X Y for a Hermitian X (FP64): from registers on one-wave teams, staged
-// through slots s0, s1 otherwise.
-template <class G>
-__device__ __forceinline__ Tile<double> herm_mul(const Tile<double>& X, const Tile<double>& Y, const Lane& L,
-                                                 double* s0, double* s1) {
-    if constexpr (G::TW == 1) {
-        return reg_mul_herm<double>(X, Y);
-    } else {
-        team_sync<G>();
-        slot_store<G, double>(s0, X, L);
-        slot_store<G, double>(s1, Y, L);
-        team_sync<G>();
-        return slot_mul<G, double>(s0, s1, L);
-    }
-}
-
-// exp(-i theta X) for the (pre-scaled) Hermitian tile set X = G / theta,
-// spectrum in [-1, 1], by the degree-m Chebyshev series
-// J_0(theta) + 2 sum_{k>=1} (-i)^k J_k(theta) T_k(X) (eq. chebychev_series
-// with alpha = -theta, beta = theta, so the phase factor is 1), split into
-// its even and odd halves and returned in the Hermitian pair form C - i P of
-// the Taylor path.  With Y = T_2(X) = 2 X^2 - I, T_2j(X) = T_j(Y) and
-// T_{2j+1}(X) = X (2 sum_{i=1..j} (-1)^{j-i} T_i(Y) + (-1)^j I), so
-//   C = sum_{i <= m/2} e_i T_i(Y),   P = X sum_{i <= (m-1)/2} b_i T_i(Y),
-// e_0 = J_0, e_i = 2 (-1)^i J_2i, and b the alternating suffix sums of the
-// odd coefficients (row `ec` of the host's table: e, then b, kChebHalf
-// each).  The T_i(Y) follow from T_{i+1} = 2 Y T_i - T_{i-1}; every product
-// has the Hermitian left factor X or Y (registers on one-wave teams).
-// floor(m/2) + 1 products, where the Clenshaw recurrence in X takes m.  FP64.
-template <class G>
-__device__ void cheb_parts(const Tile<double>& Gt, int m, double theta, const double* ec, const Lane& L,
-                           double* s0, double* s1, Tile<double>& C, Tile<double>& P) {
-    const double inv = 1.0 / theta;
-    const double* eb = ec + kChebHalf;
-    const int qc = m / 2, qs = (m - 1) / 2;   // m >= 1
-    Tile<double> X, Sp;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const bool diag = 16 * L.TI + crow<double>(L.g, r) == 16 * L.TJ + L.j;
-        X.re[r] = Gt.re[r] * inv;
-        X.im[r] = Gt.im[r] * inv;
-        C.re[r] = diag ? ec[0] : 0.0;
-        Sp.re[r] = diag ? eb[0] : 0.0;
-        C.im[r] = Sp.im[r] = 0.0;
-    }
-    if (qc >= 1) {
-        Tile<double> Y = herm_mul<G>(X, X, L, s0, s1);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const bool diag = 16 * L.TI + crow<double>(L.g, r) == 16 * L.TJ + L.j;
-            Y.re[r] = fma(2.0, Y.re[r], diag ? -1.0 : 0.0);
-            Y.im[r] *= 2.0;
-        }
-        axpy(C, ec[1], Y);
-        if (qs >= 1) axpy(Sp, eb[1], Y);
-        if constexpr (G::TW > 1) {
-            // multi-wave teams: Y, the same left factor of every step, is
-            // staged once and read from its slot; the recurrence then holds
-            // two terms of T and no copy of Y in registers
-            team_sync<G>();
-            slot_store<G, double>(s0, Y, L);
-        }
-        Tile<double> Tm = ident<double>(L), Tc = Y;
-        for (int i = 2; i <= qc; ++i) {
-            Tile<double> Tn;
-            if constexpr (G::TW > 1) {
-                team_sync<G>();
-                slot_store<G, double>(s1, Tc, L);
-                team_sync<G>();
-                Tn = slot_mul<G, double>(s0, s1, L);
-            } else {
-                Tn = herm_mul<G>(Y, Tc, L, s0, s1);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                Tn.re[r] = fma(2.0, Tn.re[r], -Tm.re[r]);
-                Tn.im[r] = fma(2.0, Tn.im[r], -Tm.im[r]);
-            }
-            axpy(C, ec[i], Tn);
-            if (i <= qs) axpy(Sp, eb[i], Tn);
-            Tm = Tc;
-            Tc = Tn;
-        }
-    }
-    if (qs >= 1) {
-        P = herm_mul<G>(X, Sp, L, s0, s1);
-    } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            P.re[r] = eb[0] * X.re[r];
-            P.im[r] = eb[0] * X.im[r];
-        }
-    }
-}
-
-// The sixth-order Magnus exponent of a slice (three-node scheme of Blanes,
-// Casas and Ros) from its Hermitian moments P1, P2, P3 (the weights of
-// m6_weight).  With a_q = -i P_q, the scheme's
-//   C1 = [a1, a2],  C2 = -(1/60) [a1, 2 a3 + C1],
-//   Omega = a1 + a3 / 12 + (1/240) [-20 a1 - a3 + C1, a2 + C2]
-// reads, on Hermitian R1 = i C1 and R2 = i C2 and G = i Omega,
-//   R1 = -i [P1, P2],  R2 = (i/60) [P1, 2 P3 + R1],
-//   G = P1 + P3 / 12 - (i/240) [-20 P1 - P3 + R1, P2 + R2],
-// three commutators of Hermitian matrices, each one product and an adjoint.
-// Uses slots s0, s1.
-template <class G>
-__device__ Tile<double> magnus6_exponent(const Tile<double>& P1, const Tile<double>& P2, const Tile<double>& P3,
-                                         const Lane& L, double* s0, double* s1) {
-    Tile<double> K = minus_adjoint<G>(herm_mul<G>(P1, P2, L, s0, s1), L, s0);
-    Tile<double> R1, W;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        R1.re[r] = K.im[r];
-        R1.im[r] = -K.re[r];
-        W.re[r] = 2.0 * P3.re[r] + R1.re[r];
-        W.im[r] = 2.0 * P3.im[r] + R1.im[r];
-    }
-    K = minus_adjoint<G>(herm_mul<G>(P1, W, L, s0, s1), L, s0);
-    Tile<double> X, Y;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        X.re[r] = (-20.0 * P1.re[r] - P3.re[r]) + R1.re[r];
-        X.im[r] = (-20.0 * P1.im[r] - P3.im[r]) + R1.im[r];
-        Y.re[r] = P2.re[r] - K.im[r] * (1.0 / 60.0);
-        Y.im[r] = P2.im[r] + K.re[r] * (1.0 / 60.0);
-    }
-    K = minus_adjoint<G>(herm_mul<G>(X, Y, L, s0, s1), L, s0);
-    Tile<double> Gt;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        Gt.re[r] = (P1.re[r] + P3.re[r] * (1.0 / 12.0)) + K.im[r] * (1.0 / 240.0);
-        Gt.im[r] = (P1.im[r] + P3.im[r] * (1.0 / 12.0)) - K.re[r] * (1.0 / 240.0);
-    }
-    return Gt;
 }
 
 }  // namespace

@@ -18,7 +18,6 @@
 namespace pm {
 hipError_t launch_mfma(int D, int precision, const PropParams& p, hipStream_t stream);
 hipError_t launch_valu(int D, bool fp64, const PropParams& p, hipStream_t stream);
-int mfma_chains_per_block(int D);
 hipError_t launch_backward(int D, const GradParams& gp, double* grad_samples, hipStream_t stream);
 hipError_t launch_batch(int precision, const BatchParams& bp, int blocks, hipStream_t stream);
 hipError_t batch_setup(int precision);
@@ -38,10 +37,14 @@ struct pm_ctx {
     pm::EngineInfo eng{};
     std::vector<double> basis;   // FP64 [M][dim][dim] interleaved
     std::vector<double> norms;   // [M]
+    std::vector<float> beta;     // [M] bounds of the 2-norms (tile engines)
     uint8_t pair_a[pm::kMaxBasis] = {};
     uint8_t pair_b[pm::kMaxBasis] = {};
     double theta[pm::kMaxDeg + 1] = {};
     int64_t theta_n = -1;        // slice count the theta table was made for
+    int64_t scheme_n = -1;       // slice count and degree cap of the scheme table
+    int scheme_cap = 0;
+    pm::PropParams schemes{};    // holds sth, tc and qmax
     int max_degree = PM_MAX_TAYLOR_DEGREE;
     int force_s = -1;
     int64_t chunk_override = 0;
@@ -198,6 +201,31 @@ void fill_theta(double* theta, int precision, int64_t n) {
     for (int m = 1; m <= pm::kMaxDeg; ++m) theta[m] = taylor_theta(m, u, relative_truncation(precision));
 }
 
+// The tile engines' series: scheme q's threshold is the largest ||G||_2 whose
+// remainder stays below the rounding of the whole propagation.  The bound that
+// is compared with it is close to the 2-norm (a 1-norm is several times it),
+// so the target keeps an eighth of u / sqrt(N): truncation errors of
+// neighbouring slices add coherently, rounding errors like sqrt(N).  Reduced
+// precisions: relative to ||G||, and no scheme past degree 12 (||G|| ~ 1),
+// where terms grow well past the result.
+void fill_schemes(pm::PropParams& p, int precision, int64_t n, int max_degree) {
+    const double u = std::max(std::ldexp(1.0, -60),
+                              unit_roundoff(precision) / (8.0 * std::sqrt((double)std::max<int64_t>(n, 1))));
+    p.qmax = 0;
+    for (int q = 0; q < pm::kSchemes; ++q) {
+        const bool in = (q == 0 || pm::scheme_degree(q - 1) < max_degree) &&
+                        (precision == PM_FP64 || pm::scheme_degree(q) <= 12);
+        p.sth[q] = in ? taylor_theta(std::min(pm::scheme_degree(q), max_degree), u, relative_truncation(precision))
+                      : -1.0;
+        if (in) p.qmax = q;
+    }
+    double f = 1.0;
+    for (int k = 0; k <= pm::scheme_degree(pm::kSchemes - 1); ++k) {
+        if (k > 0) f /= k;
+        p.tc[k] = k <= max_degree ? f : 0.0;
+    }
+}
+
 // Lubich's estimate of the Chebyshev truncation error (eq. error_chebychev)
 // for degree m and spectral width w = beta - alpha.
 double lubich_error(int m, double w) {
@@ -299,6 +327,44 @@ double norm1(const Mat& a, int64_t d) {
         best = std::max(best, s);
     }
     return best;
+}
+
+// Upper bound of ||A||_2 of a Hermitian A: (||A^n||_F)^(1/n), n = 2^k by
+// repeated squaring of the scaled matrix (within d^(1/2n) of the 2-norm:
+// n = 64 2 % at d = 16, n = 16 14 % at d = 64), never above ||A||_1.
+float norm2_bound(const Mat& a, int64_t d) {
+    const double n1 = norm1(a, d);
+    if (!(n1 > 0.0)) return 0.0f;
+    const int squarings = d <= 16 ? 6 : (d <= 32 ? 5 : 4);
+    std::vector<double> x((size_t)(2 * d * d)), y(x.size());
+    for (int64_t i = 0; i < d * d; ++i) {
+        x[2 * i] = a[i].real() / n1;
+        x[2 * i + 1] = a[i].imag() / n1;
+    }
+    double lg = 0.0;   // log of the scale taken out of A^n / n1^n
+    for (int k = 0; k < squarings; ++k) {
+        // A A = A A^H: entry (i, j) from rows i and j
+        double f = 0.0;
+        for (int64_t i = 0; i < d; ++i)
+            for (int64_t j = i; j < d; ++j) {
+                const double *u = &x[2 * i * d], *v = &x[2 * j * d];
+                double re = 0.0, im = 0.0;
+                for (int64_t q = 0; q < d; ++q) {
+                    re += u[2 * q] * v[2 * q] + u[2 * q + 1] * v[2 * q + 1];
+                    im += u[2 * q + 1] * v[2 * q] - u[2 * q] * v[2 * q + 1];
+                }
+                y[2 * (i * d + j)] = y[2 * (j * d + i)] = re;
+                y[2 * (i * d + j) + 1] = im;
+                y[2 * (j * d + i) + 1] = -im;
+                f += (i == j ? 1.0 : 2.0) * (re * re + im * im);
+            }
+        f = std::sqrt(f);
+        if (!(f > 0.0)) return (float)(n1 * (1.0 + 1e-6));
+        lg = 2.0 * lg + std::log(f);
+        for (double& v : y) v /= f;
+        x.swap(y);
+    }
+    return (float)(std::min(n1, n1 * std::exp(lg / (1 << squarings))) * (1.0 + 1e-6));
 }
 
 // The ordered basis: H0, H_1..H_K [, i[H0,H_k] (k=1..K), i[H_k,H_k'] (k<k')].
@@ -658,6 +724,7 @@ pm_status prepare(pm_ctx* ctx, const pm::EngineInfo& e, bool keep_nodes, const d
     p.n_long = 0;
     p.n_chains = chains;
     p.n_leaves = leaves;
+    p.chains_per_leaf = e.chains_per_leaf;
     if (!keep_nodes) skew_chains(ctx, e, p);
     p.slices_out = d_slices;
     p.nodes = nodes;
@@ -669,6 +736,17 @@ pm_status prepare(pm_ctx* ctx, const pm::EngineInfo& e, bool keep_nodes, const d
         ctx->theta_n = N;
     }
     std::memcpy(p.theta, ctx->theta, sizeof(p.theta));
+    if (e.kind == pm::ENGINE_MFMA) {
+        if (ctx->scheme_n != N || ctx->scheme_cap != ctx->max_degree) {
+            fill_schemes(ctx->schemes, ctx->precision, N, ctx->max_degree);
+            ctx->scheme_n = N;
+            ctx->scheme_cap = ctx->max_degree;
+        }
+        std::memcpy(p.sth, ctx->schemes.sth, sizeof(p.sth));
+        std::memcpy(p.tc, ctx->schemes.tc, sizeof(p.tc));
+        p.qmax = ctx->schemes.qmax;
+        for (int m = 0; m < ctx->M; ++m) p.beta[m] = ctx->beta[m];
+    }
     p.K = (int)ctx->n_ctrl;
     p.M = ctx->M;
     p.order = ctx->order;
@@ -787,7 +865,8 @@ bool pick_engine(int du, int precision, EngineInfo* out) {
         e.kind = ENGINE_MFMA;
         e.D = du <= 16 ? 16 : (du <= 32 ? 32 : 64);
         e.chunk_unit = 1;
-        e.chains_per_leaf = mfma_chains_per_block(e.D);   // a block is a leaf
+        // a block is a leaf: four one-wave teams, or one larger team
+        e.chains_per_leaf = e.D == 16 || (e.D == 32 && precision == PM_FP64) ? 4 : 1;
         e.resident_chains = e.D == 16 ? 256 * 8 : (e.D == 32 ? 256 * 4 : 256);
         e.f64_rows = precision == PM_FP64 ? 1 : 0;
     }
@@ -1237,6 +1316,10 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
     ctx->eng = e;
     ctx->basis = flat;
     ctx->norms = norms;
+    ctx->beta.resize(M);
+    // (the commutators' weights are small: their 1-norm serves)
+    for (int m = 0; m < M; ++m)
+        ctx->beta[m] = m <= n_ctrl ? norm2_bound(basis[m], dim) : (float)(norms[m] * (1.0 + 1e-6));
     std::memset(ctx->pair_a, 0, sizeof(ctx->pair_a));
     std::memset(ctx->pair_b, 0, sizeof(ctx->pair_b));
     for (size_t q = 0; q < pairs.size(); ++q) {

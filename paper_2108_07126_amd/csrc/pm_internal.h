@@ -22,6 +22,12 @@ constexpr int kOrderM6 = PM_ORDER_MAGNUS6; // sixth-order Magnus, three samples 
 constexpr int kFanIn = 8;                  // fan-in of the MFMA engines' product tree
 constexpr int kFanInLog2 = 3;
 
+// Evaluation schemes of the series exp(i G) on the tile engines (powers in
+// blocks of three, Paterson-Stockmeyer): scheme q takes q products and
+// reaches degree 1, 2, 4, 6, 9, 12, 15.
+constexpr int kSchemes = 7;
+constexpr int scheme_degree(int q) { return q < 2 ? q + 1 : (q == 2 ? 4 : 3 * (q - 1)); }
+
 // Everything one propagation launch needs, passed by value as the kernel
 // argument.  Pointers are device pointers.
 struct PropParams {
@@ -33,7 +39,8 @@ struct PropParams {
     int64_t n_long;           // the first n_long chains hold chunk_long slices each (0: none)
     int64_t chunk_long;
     int64_t n_chains;         // chains covering the N slices
-    int64_t n_leaves;         // leaves of the product tree (blocks or waves)
+    int64_t n_leaves;         // leaves of the product tree (blocks)
+    int chains_per_leaf;      // consecutive chains combined into a leaf
     void* slices_out;         // nullptr or [N][du][du] complex (c128 / c64)
     double* nodes;            // tree nodes, [2 * n_leaves][D][D] complex128
     unsigned* counters;       // [2 * n_leaves] pair tickets, zero between launches
@@ -42,6 +49,10 @@ struct PropParams {
     int store_nodes;          // keep every tree node (gradient checkpoints)
     double h;
     double theta[kMaxDeg + 1];   // Taylor thresholds for the working precision
+    double sth[kSchemes];        // largest ||G||_2 for scheme q (-1: past the degree cap)
+    int qmax;                    // the last available scheme
+    double tc[scheme_degree(kSchemes - 1) + 1];   // 1/k!, zero past the degree cap
+    float beta[kMaxBasis];       // upper bounds of ||B_m||_2
     int K, M, order, du;
     int max_degree, force_s;
     int basis_lds;               // MFMA engine: block keeps a copy of the basis in LDS

@@ -1,0 +1,110 @@
+"""The FP64 tile engines where their instances change: the k-slices that a
+dimension reaches (9, 12 | 13, 16 | 17, 24 | 25, 32 | 33, 40 | 41 .. 64), the
+basis sizes at which LDS is left or a commutator is formed by product, every
+evaluation scheme of the series and its degree cap, and squarings.
+
+Tolerances: an FP64 product of d x d unitary-scale matrices rounds to about
+sqrt(d) 2^-53 in relative Frobenius norm and a propagation of n slices takes
+at most a few products per slice beside its chain product, errors adding like a
+random walk; 64 sqrt(n d) 2^-53 leaves a margin of several times, and a slice
+or k-slice left out differs by far more.
+"""
+import math
+import sys
+
+import numpy as np
+import pytest
+
+import oracle.propagator as orc
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2108_07126_amd as m
+    return m
+
+
+def check(pm, w, slices=True, s=0, **policy):
+    print(f"[case] d={w.dim} K={w.n_ctrl} N={w.n_slices} order={w.order} {policy}", file=sys.stderr, flush=True)
+    with pm.Context(0, pm.PM_FP64) as ctx:
+        ctx.set_hamiltonian(w.H0, w.Hk, w.order)
+        if policy:
+            ctx.set_expm_policy(**policy)
+        U, sl = ctx.equiprop(w.samples, w.h, return_slices=True) if slices else (ctx.equiprop(w.samples, w.h), None)
+    out = orc.propagate(w.H0, w.Hk, w.samples, w.h, w.order, return_slices=slices)
+    Uo, slo = out if slices else (out, None)
+    n, d = w.n_slices, w.dim
+    tol = 64 * math.sqrt(n * d) * 2.0 ** -53 * 2 ** s
+    err = orc.relative_frobenius(U, Uo)
+    print(f"  error {err:.2e} (bound {tol:.2e})", file=sys.stderr, flush=True)
+    assert err <= tol
+    if slices:
+        assert np.max(np.abs(sl - slo)) <= 64 * math.sqrt(d) * 2.0 ** -53 * 2 ** s
+
+
+@pytest.mark.parametrize("d", [7, 8, 9, 12, 13, 16, 17, 24, 25, 32, 33, 40, 41, 48, 49, 56, 57, 64])
+def test_dimension_edges(pm, d):
+    for n, order in ((1, 2), (6, 4), (300, 2)):
+        check(pm, synth.random_system(d, 2, n_slices=n, h=0.03, order=order, tag=700 + d))
+
+
+@pytest.mark.parametrize("d,K", [(6, 4), (8, 5), (8, 6), (8, 7), (16, 4), (16, 5), (24, 2), (24, 3), (32, 7), (32, 8), (64, 3), (64, 4)])
+def test_basis_sizes(pm, d, K):
+    """Fourth order with 15, 21, 28, 36, .. basis matrices (in LDS, in memory, by
+    one commutator), second order with 8 and 9."""
+    for order in (2, 4):
+        check(pm, synth.random_system(d, K, n_slices=41, h=0.03, order=order, tag=740 + d))
+
+
+@pytest.mark.parametrize("d", [8, 11, 16, 27, 64])
+@pytest.mark.parametrize("norm", [1e-9, 1e-5, 1e-3, 0.02, 0.1, 0.4, 2.0])
+def test_schemes(pm, d, norm):
+    """Slice norms that take each evaluation scheme, the last with squarings."""
+    s = max(0, math.ceil(math.log2(norm / 0.3)))
+    check(pm, synth.random_system(d, 1, n_slices=23, h=norm, order=2, tag=760), s=s)
+
+
+@pytest.mark.parametrize("d", [8, 16, 32, 64])
+def test_degree_caps_and_forced_squarings(pm, d):
+    """Each degree cap leaves the series enough squarings; fixed squarings."""
+    w = synth.random_system(d, 2, n_slices=9, h=0.2, order=4, tag=780)
+    for cap in (2, 3, 4, 5, 7, 12, 14):
+        # a degree-cap remainder below 2^-56 at ||G|| ~ 0.5: log2(0.5 / theta)
+        s = max(0, math.ceil(math.log2(0.5 / (2.0 ** -56 * math.factorial(cap + 1)) ** (1.0 / (cap + 1)))))
+        check(pm, w, max_taylor_degree=cap, s=s)
+    check(pm, w, force_s=5, s=5)
+
+
+@pytest.mark.parametrize("d", [16, 32, 64])
+def test_cancelling_terms(pm, d):
+    """A drift and a control that cancel: the bound by the terms asks for
+    squarings that the exponent's own norm does not."""
+    w = synth.random_system(d, 2, n_slices=40, h=0.05, order=2, tag=790)
+    H0, Hk = 400.0 * w.Hk[1] + w.H0, w.Hk.copy()
+    w.samples[1] = -400.0
+    class _W:
+        pass
+    x = _W()
+    x.__dict__.update(w.__dict__, H0=H0, Hk=Hk, dim=d, n_ctrl=2, n_slices=40)
+    # the exponents themselves round at the terms' scale: 20 instead of 0.05
+    check(pm, x, s=9)
+
+
+@pytest.mark.parametrize("d", [16, 32, 64])
+def test_ragged_trees(pm, d):
+    """Chains that leave blocks and tree groups partly filled."""
+    for chains in (1, 2, 3, 5, 9, 33, 65, 66):
+        w = synth.random_system(d, 1, n_slices=3 * chains - 1 if chains > 1 else 2, h=0.02, order=2, tag=800 + chains)
+        print(f"[case] tree d={d} chains={chains}", file=sys.stderr, flush=True)
+        with pm.Context(0, pm.PM_FP64) as ctx:
+            ctx.set_hamiltonian(w.H0, w.Hk, 2)
+            ctx.set_chunk(3)
+            U = ctx.equiprop(w.samples, w.h)
+        Uo = orc.propagate(w.H0, w.Hk, w.samples, w.h, 2)
+        assert orc.relative_frobenius(U, Uo) <= 64 * math.sqrt(w.n_slices * d) * 2.0 ** -53, chains
