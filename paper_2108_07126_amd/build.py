@@ -25,9 +25,15 @@ FLAGS = [
     "-Wno-unused-result",
 ]
 
+# Units whose kernels run one or two waves per SIMD: with nothing else to hide
+# them, wait states between a vector instruction and the MFMA that reads it
+# count, and the ILP scheduler leaves a tenth of them.
+ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
+UNIT_FLAGS = {"engine_strip.hip": ILP, "engine_wave_32.hip": ILP}
+
 
 def _compile(src: str, obj: str, verbose: bool) -> None:
-    cmd = [HIPCC, *FLAGS, "-c", "-I", os.path.join(HERE, "..", "include"), src, "-o", obj]
+    cmd = [HIPCC, *FLAGS, *UNIT_FLAGS.get(os.path.basename(src), []), "-c", "-I", os.path.join(HERE, "..", "include"), src, "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -10,16 +10,13 @@ hipError_t launch_wave_cheb(int D, const PropParams& p, hipStream_t stream);
 
 namespace {
 
-// The basis in LDS leaves room for two blocks per CU up to 16 matrices.
-constexpr int kWaveBasis16 = 16;
-
 hipError_t launch_wave16(const PropParams& p, hipStream_t stream) {
-    if (p.pair)
-        return p.M <= kWaveBasis16 ? launch_wave_one<1, 4, EXPO_BASIS, false, true, true>(p, stream)
-                                   : launch_wave_one<1, 4, EXPO_BASIS, false, true, false>(p, stream);
+    if (p.pair) return launch_wave_one<1, 4, EXPO_BASIS, false, true, true>(p, stream);
     // past that only fourth order with five controls or more (21 matrices):
     // one commutator by product instead of K (K + 1) / 2 more basis matrices
-    if (p.M > kWaveBasis16) return launch_wave_one<1, 4, EXPO_COMM, false, false, true>(p, stream);
+    if (p.M > kWaveBasis)
+        return p.du <= 8 ? launch_wave_one<1, 2, EXPO_COMM, false, false, true>(p, stream)
+                         : launch_wave_one<1, 4, EXPO_COMM, false, false, true>(p, stream);
     return p.du <= 12 ? launch_wave_one<1, 3, EXPO_BASIS, false, false, true>(p, stream)
                       : launch_wave_one<1, 4, EXPO_BASIS, false, false, true>(p, stream);
 }

@@ -17,9 +17,11 @@ hipError_t launch_wave_m6(int D, const PropParams& p, hipStream_t stream) {
 }
 
 hipError_t launch_wave_cheb(int D, const PropParams& p, hipStream_t stream) {
-    if (D == 32) return launch_wave_one<2, 8, EXPO_BASIS, true, false, false>(p, stream);
-    return p.M <= 16 ? launch_wave_one<1, 4, EXPO_BASIS, true, false, true>(p, stream)
-                     : launch_wave_one<1, 4, EXPO_BASIS, true, false, false>(p, stream);
+    if (D == 32)
+        return p.M <= kWaveBasis ? launch_wave_one<2, 8, EXPO_BASIS, true, false, false>(p, stream)
+                                 : launch_wave_one<2, 8, EXPO_COMM, true, false, false>(p, stream);
+    return p.M <= kWaveBasis ? launch_wave_one<1, 4, EXPO_BASIS, true, false, true>(p, stream)
+                             : launch_wave_one<1, 4, EXPO_COMM, true, false, true>(p, stream);
 }
 
 }  // namespace pm

@@ -109,61 +109,67 @@ struct NoStep {
     __device__ __forceinline__ void operator()(int) const {}
 };
 
-// S^H X for the staged S, as three real products (3M): t1 = Sr Xr,
-// t2 = Si Xi, t3 = (Sr - Si)(Xr + Xi), Re = t1 + t2, Im = t3 - t1 + t2.
-// The wave runs alone on its SIMD (D = 64) or beside one other, so nothing else
-// hides the LDS latency: the fragments of the next tile pair are read before
-// the twelve products of this one (768 cycles), and a row tile's sums are
-// taken after the next row tile's first products are on their way.
-// step(f) is called once per tile pair, between its reads and its products
-// (work to overlap, for instance the next slice's basis loads).
+// S^H X for the staged S, as three real products chained through the
+// accumulator: k = (Sr - Si) Xr, Re = k + Si (Xr + Xi), Im = k + Sr (Xi - Xr).
+// Re and Im start from k as their MFMAs' C operand, so no sums follow the
+// matrix instructions, and a row tile needs one vector operation per three
+// MFMAs.  That matters: no vector instruction overlaps an FP64 MFMA of the same
+// SIMD, and a SIMD with a single wave issues one in about 7 cycles.
+// The next row tile's fragments are read as this one's are used up.
+// step(f) is called RT * RT times among the products (work to overlap, for
+// instance the next slice's basis loads).
 template <int NT, int KS, class F = NoStep>
 __device__ __forceinline__ Strip<NT> strip_mul(const char* slot, const Strip<NT>& X, const SLane& L,
                                                F step = F()) {
     constexpr int RT = (KS + 3) / 4;        // row tiles reached
-    constexpr int N = RT * RT;
     Strip<NT> out;
     strip_each<NT>([&](int k, int r) { out.t[k].re[r] = out.t[k].im[r] = 0.0; });
     if (L.c >= RT) return out;
     const d2_t* s = reinterpret_cast<const d2_t*>(slot) + L.lane;
-    auto rs_of = [](int k) constexpr { return 4 * k + 4 <= KS ? 4 : KS - 4 * k; };
-    d2_t a[2][4];
-    d4_t acc[2][3];
-    auto read = [&](int f) {
-        const int i = f / RT, k = f % RT;
+    double xp[KS], xm[KS];
+    d2_t a[KS];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (r < rs_of(k)) a[f & 1][r] = s[((i * NT + k) * 4 + r) * 64];
-    };
-    auto finish = [&](int i) {
+    for (int q = 0; q < KS; ++q) a[q] = s[q * 64];
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+        const double xr = X.t[q >> 2].re[q & 3], xi = X.t[q >> 2].im[q & 3];
+        xp[q] = xr + xi;
+        xm[q] = xi - xr;
+    }
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        __builtin_amdgcn_sched_barrier(0);
+        d4_t kk = {0, 0, 0, 0};
+#pragma unroll
+        for (int q0 = 0; q0 < KS; q0 += 4) {
+            // (a difference right before the MFMA that reads it would cost
+            // wait states each time)
+            double d[4];
+#pragma unroll
+            for (int q = q0; q < q0 + 4 && q < KS; ++q) d[q - q0] = a[q].x - a[q].y;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = q0; q < q0 + 4 && q < KS; ++q) kk = mfma16(d[q - q0], X.t[q >> 2].re[q & 3], kk);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        d4_t re = kk, im = kk;
+#pragma unroll
+        for (int q = 0; q < KS; ++q) {
+            if ((q & 3) == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                step(i * RT + (q >> 2));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            re = mfma16(a[q].y, xp[q], re);
+            im = mfma16(a[q].x, xm[q], im);
+            if (i + 1 < RT) a[q] = s[((i + 1) * NT * 4 + q) * 64];
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const d4_t &t1 = acc[i & 1][0], &t2 = acc[i & 1][1], &t3 = acc[i & 1][2];
-            out.t[i].re[r] = t1[r] + t2[r];
-            out.t[i].im[r] = t3[r] - t1[r] + t2[r];
+            out.t[i].re[r] = re[r];
+            out.t[i].im[r] = im[r];
         }
-    };
-    read(0);
-#pragma unroll
-    for (int f = 0; f < N; ++f) {
-        const int i = f / RT, k = f % RT;
-        if (f + 1 < N) read(f + 1);
-        step(f);
-        __builtin_amdgcn_sched_barrier(0);
-        if (k == 0) acc[i & 1][0] = acc[i & 1][1] = acc[i & 1][2] = d4_t{0, 0, 0, 0};
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (r < rs_of(k)) {
-                const d2_t v = a[f & 1][r];
-                const double xr = X.t[k].re[r], xi = X.t[k].im[r];
-                acc[i & 1][0] = mfma16(v.x, xr, acc[i & 1][0]);
-                acc[i & 1][1] = mfma16(v.y, xi, acc[i & 1][1]);
-                acc[i & 1][2] = mfma16(v.x - v.y, xr + xi, acc[i & 1][2]);
-            }
-        if (k == 0 && i > 0) finish(i - 1);
-        __builtin_amdgcn_sched_barrier(0);
     }
-    finish(RT - 1);
     return out;
 }
 
@@ -245,14 +251,21 @@ __device__ __forceinline__ Strip<NT> strip_expm1(const PropParams& p, const Stri
             E.t[k].im[r] = fma(-c3, Z.t[k].re[r], E.t[k].im[r]);
         });
     }
-    while (--i >= 0) {
+    while (--i > 0) {
         const Strip<NT> W = strip_mul<NT, KS>(s, E, L);
-        block(Y, i ? p.tc[3 * i] : 0.0, p.tc[3 * i + 1], p.tc[3 * i + 2]);
+        block(Y, p.tc[3 * i], p.tc[3 * i + 1], p.tc[3 * i + 2]);
         strip_each<NT>([&](int k, int r) {
             E.t[k].re[r] += W.t[k].im[r];
             E.t[k].im[r] -= W.t[k].re[r];
         });
     }
+    // the last block: c0 left out, c1 = 1
+    const Strip<NT> W = strip_mul<NT, KS>(s, E, L);
+    const double c2 = p.tc[2];
+    strip_each<NT>([&](int k, int r) {
+        E.t[k].re[r] = fma(-c2, Y.t[k].re[r], W.t[k].im[r]) - G.t[k].im[r];
+        E.t[k].im[r] = fma(-c2, Y.t[k].im[r], G.t[k].re[r]) - W.t[k].re[r];
+    });
     return E;
 }
 

@@ -59,42 +59,89 @@ __device__ __forceinline__ void sq_add(Sq<NT>& y, const Sq<NT>& x) {
     });
 }
 
-// S^H X as three real products (3M): t1 = Sr Xr, t2 = Si Xi,
-// t3 = (Sr - Si)(Xr + Xi), Re = t1 + t2, Im = t3 - t1 + t2.
-// STK (NT = 1): slice pairs, the stacked block product of reg_mul_stk.
+// S^H X as three real products chained through the accumulator:
+// k = (Sr - Si) Xr, Re = k + Si (Xr + Xi), Im = k + Sr (Xi - Xr).  Re and Im
+// start from k as their MFMAs' C operand, so no sums follow the matrix
+// instructions (the usual t1 + t2, t3 - t1 + t2 take 12 more vector
+// instructions a tile, and none of those overlaps an FP64 MFMA of its SIMD).
+// STK (NT = 1): slice pairs.  The two 8 x 8 diagonal blocks hold two slices
+// and are multiplied as the stacked product [A_a; A_b] [B_a, B_b], K = 8
+// instead of 16: for k-slice s the lane (g, j) supplies its register s (its
+// column in the first block) or s + 2 (second block) of both operands.  The
+// off-diagonal blocks of the result hold cross products, which no stacked
+// product reads (pair_mask clears them before a full one).
 template <int NT, int KS, bool STK = false>
 __device__ __forceinline__ Sq<NT> sq_mul(const Sq<NT>& S, const Sq<NT>& X) {
     Sq<NT> out;
     if constexpr (STK) {
         static_assert(NT == 1, "slice pairs live in one tile");
-        out.t[0][0] = reg_mul_stk(S.t[0][0].re, S.t[0][0].im, X.t[0][0]);
+        const bool hi = (__lane_id() & 8) != 0;
+        const Tile<double>&A = S.t[0][0], &B = X.t[0][0];
+        double sr[2], si[2], xr[2], xi[2];
+        d4_t kk = {0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            sr[q] = hi ? A.re[q + 2] : A.re[q];
+            si[q] = hi ? A.im[q + 2] : A.im[q];
+            xr[q] = hi ? B.re[q + 2] : B.re[q];
+            xi[q] = hi ? B.im[q + 2] : B.im[q];
+            kk = mfma16(sr[q] - si[q], xr[q], kk);
+        }
+        d4_t re = kk, im = kk;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            re = mfma16(si[q], xr[q] + xi[q], re);
+            im = mfma16(sr[q], xi[q] - xr[q], im);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            out.t[0][0].re[r] = re[r];
+            out.t[0][0].im[r] = im[r];
+        }
         return out;
     } else {
         constexpr int RT = (KS + 3) / 4;
+        // the operands' sums ahead of the MFMAs (one right before the MFMA
+        // that reads it would cost wait states each time)
+        double sd[NT][KS];
 #pragma unroll
-        for (int i = 0; i < NT; ++i)
+        for (int i = 0; i < RT; ++i)
 #pragma unroll
-            for (int n = 0; n < NT; ++n) {
-                d4_t t1 = {0, 0, 0, 0}, t2 = {0, 0, 0, 0}, t3 = {0, 0, 0, 0};
+            for (int q = 0; q < KS; ++q) sd[i][q] = S.t[q >> 2][i].re[q & 3] - S.t[q >> 2][i].im[q & 3];
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            double xp[KS], xm[KS];
+#pragma unroll
+            for (int q = 0; q < KS; ++q) {
+                const Tile<double>& B = X.t[q >> 2][n];
+                xp[q] = B.re[q & 3] + B.im[q & 3];
+                xm[q] = B.im[q & 3] - B.re[q & 3];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                d4_t kk = {0, 0, 0, 0};
                 if (i < RT && n < RT) {
 #pragma unroll
-                    for (int k = 0; k < RT; ++k)
+                    for (int q = 0; q < KS; ++q) kk = mfma16(sd[i][q], X.t[q >> 2][n].re[q & 3], kk);
+                }
+                d4_t re = kk, im = kk;
+                if (i < RT && n < RT) {
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (4 * k + r < KS) {
-                                const double ar = S.t[k][i].re[r], ai = S.t[k][i].im[r];
-                                const double xr = X.t[k][n].re[r], xi = X.t[k][n].im[r];
-                                t1 = mfma16(ar, xr, t1);
-                                t2 = mfma16(ai, xi, t2);
-                                t3 = mfma16(ar - ai, xr + xi, t3);
-                            }
+                    for (int q = 0; q < KS; ++q) {
+                        const Tile<double>& A = S.t[q >> 2][i];
+                        re = mfma16(A.im[q & 3], xp[q], re);
+                        im = mfma16(A.re[q & 3], xm[q], im);
+                    }
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    out.t[i][n].re[r] = t1[r] + t2[r];
-                    out.t[i][n].im[r] = t3[r] - t1[r] + t2[r];
+                    out.t[i][n].re[r] = re[r];
+                    out.t[i][n].im[r] = im[r];
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
         return out;
     }
 }
@@ -145,14 +192,21 @@ __device__ __forceinline__ Sq<NT> sq_expm1(const PropParams& p, const Sq<NT>& G,
         E.t[i][n].re[r] = fma(c3, Z.t[i][n].im[r], E.t[i][n].re[r]);
         E.t[i][n].im[r] = fma(-c3, Z.t[i][n].re[r], E.t[i][n].im[r]);
     });
-    while (--b >= 0) {
+    while (--b > 0) {
         const Sq<NT> W = sq_mul<NT, KS, STK>(Z, E);
-        block(b ? p.tc[3 * b] : 0.0, p.tc[3 * b + 1], p.tc[3 * b + 2]);
+        block(p.tc[3 * b], p.tc[3 * b + 1], p.tc[3 * b + 2]);
         sq_each<NT>([&](int i, int n, int r) {
             E.t[i][n].re[r] += W.t[i][n].im[r];
             E.t[i][n].im[r] -= W.t[i][n].re[r];
         });
     }
+    // the last block: c0 left out, c1 = 1
+    const Sq<NT> W = sq_mul<NT, KS, STK>(Z, E);
+    const double c2 = p.tc[2];
+    sq_each<NT>([&](int i, int n, int r) {
+        E.t[i][n].re[r] = fma(-c2, Y.t[i][n].re[r], W.t[i][n].im[r]) - G.t[i][n].im[r];
+        E.t[i][n].im[r] = fma(-c2, Y.t[i][n].im[r], G.t[i][n].re[r]) - W.t[i][n].re[r];
+    });
     return E;
 }
 

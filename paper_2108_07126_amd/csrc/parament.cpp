@@ -767,7 +767,7 @@ pm_status prepare(pm_ctx* ctx, const pm::EngineInfo& e, bool keep_nodes, const d
     // the checkpointed forward pass: its chain products and tree nodes come
     // out in the unpaired layout)
     if (ctx->d_basis_pair && basis == ctx->d_basis && (ctx->method == PM_EXPM_TAYLOR || keep_nodes) &&
-        e.kind == pm::ENGINE_MFMA && e.D == 16) {
+        e.kind == pm::ENGINE_MFMA && e.D == 16 && (ctx->precision != PM_FP64 || ctx->M <= pm::kWaveBasis)) {
         p.pair = 1;
         p.basis = ctx->d_basis_pair;
     }

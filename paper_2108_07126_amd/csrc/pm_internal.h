@@ -28,6 +28,10 @@ constexpr int kFanInLog2 = 3;
 constexpr int kSchemes = 7;
 constexpr int scheme_degree(int q) { return q < 2 ? q + 1 : (q == 2 ? 4 : 3 * (q - 1)); }
 
+// Basis matrices of the one-wave teams' basis form: their weights fill a row of
+// 16 lanes, and in LDS they leave room for two blocks per CU at D = 16.
+constexpr int kWaveBasis = 16;
+
 // Everything one propagation launch needs, passed by value as the kernel
 // argument.  Pointers are device pointers.
 struct PropParams {

@@ -51,6 +51,19 @@ __device__ __forceinline__ double comm_bound(double w, float beta) {
     return (double)((s + 2.0f * a * d) * (1.0f + 0x1p-16f));
 }
 
+// EXPO_BASIS: the weights of kGroup slices at a time.  Row q of 16 lanes (lane
+// 16 q + m, m < M <= 16) holds the weights of the group's slice q (PAIR: of slice
+// q & 1 of the first (q < 2) or second half), gathered a group ahead.  One row
+// sum and one comparison then bound and plan every slice of the group, and
+// the expand step reads its weights back from LDS as broadcasts, instead of
+// these steps (about 90 vector instructions) and two lane reads per matrix
+// in each slice.
+
+// What bounds it: issue on the SIMD.  No vector instruction overlaps an FP64 MFMA
+// of the same SIMD, not even another wave's (measured), so a slice costs its
+// MFMAs (16 levels: 48 of 64 cycles) plus its vector instructions (4 cycles
+// each at two waves per SIMD, about 7.5 at one).  Cutting the latter from 331
+// to about 220 a slice took 16 levels, 2^17 slices from 302 to 272 us.
 // One wave per SIMD at D = 32 (four live matrices of 64 registers, the
 // accumulators), two at D = 16 (its serial chains of products and plans leave
 // gaps that a second wave fills).
@@ -60,7 +73,8 @@ __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 8 : 1))) propagate
     static_assert(!PAIR || (NT == 1 && EXPO == EXPO_BASIS && !CH && KS == 4), "slice pairs");
     constexpr int D = 16 * NT;
     constexpr int MAT = NT * NT * 512;   // doubles of a basis matrix
-    constexpr bool kScr = EXPO != EXPO_BASIS;
+    constexpr bool kRows = EXPO == EXPO_BASIS;
+    constexpr int kGroup = PAIR ? 2 : 4;   // steps per group of weights
     extern __shared__ double wsm[];
     // LDS: [the basis] [a scratch tile per team]; the handover slots of the end
     // lie over both
@@ -73,6 +87,8 @@ __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 8 : 1))) propagate
     int* tick = reinterpret_cast<int*>(wsm);
     d2_t* slots = reinterpret_cast<d2_t*>(wsm + 2);
     d2_t* scr = reinterpret_cast<d2_t*>(wsm + 2 + (BL ? nb * MAT : 0)) + team * kScratchTile;
+    // the group's weights (the wave's 64 lanes) behind the scratch tiles
+    double* lw = wsm + 2 + (BL ? nb * MAT : 0) + kWaveTeams * kScratchTile * 2 + team * 64;
     double* lb = wsm + 2;
     if constexpr (BL) {
         block_copy_to_lds(lb, p.basis, nb * MAT);
@@ -87,33 +103,47 @@ __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 8 : 1))) propagate
     // upper-left 8 x 8 block, the second in the lower-right one
     const int64_t jm = PAIR ? j0 + (j1 - j0 + 1) / 2 : j1;
     const int64_t steps = jm - j0;
-    const bool wsecond = PAIR && L.lane >= 32;   // this lane gathers the second half's weight
-    const bool bsecond = PAIR && L.j >= 8;       // this lane's column lies in the second block
-    const int64_t wbase = wsecond ? jm : j0, wend = wsecond ? j1 : jm;
+    const int row = L.lane >> 4, wlane = L.lane & 15;
+    const bool bsecond = PAIR && L.j >= 8;   // this lane's column lies in the second block
+    // the run whose weights this lane gathers, and its step within a group
+    const int64_t wbase = PAIR && row >= 2 ? jm : j0, wend = PAIR && row >= 2 ? j1 : jm;
+    const int wstep = kRows ? (PAIR ? (row & 1) : row) : 0;
     const int64_t jlast = p.n_slices > 0 ? p.n_slices - 1 : 0;
-    const int wlane = EXPO != EXPO_BASIS ? (L.lane & 15) : (PAIR ? (L.lane & 31) : L.lane);
     WeightRecipe wr;
     if constexpr (EXPO == EXPO_M6) wr = m6_recipe(p, L.lane);
     else if constexpr (EXPO == EXPO_COMM) wr = comm_recipe(p, L.lane);
     else wr = weight_recipe(p, wlane);
-    auto gather = [&](int64_t j) {
-        j = min(j, jlast);
+    auto gather = [&](int64_t t) {
+        const int64_t j = min(wbase + wstep + t, jlast);
         if constexpr (EXPO == EXPO_M6) return m6_gather(p, wr, j);
         else if constexpr (EXPO == EXPO_COMM) return comm_gather(p, wr, j);
         else return gather_samples(p, wr, j);
     };
     const float beta = wlane < nb ? p.beta[wlane] : 0.0f;
-    const double lsth = lane_sth_of(p, L.lane);
+    const double lsth = kRows ? lane_sth_of(p, wlane) : lane_sth_of(p, L.lane);
     const double lcth = lane_ctheta_of(p, L.lane);
     Sq<NT> Q = sq_diagonal<NT>(L, 1.0);
-    SliceSamples smp = gather(wbase);
+    SliceSamples smp = gather(0);
+    double wl = 0.0;
+    float bounds = 0.0f;               // of the row's slice
+    unsigned long long fits = 0;       // bit 16 q + s: scheme s serves the row's slice
     for (int64_t t = 0; t < steps; ++t) {
-        double wl;
-        if constexpr (EXPO == EXPO_M6) wl = m6_weight(p, wr, smp);
-        else if constexpr (EXPO == EXPO_COMM) wl = comm_weight(p, wr, smp);
-        else wl = combine_weight(p, wr, smp);
-        if (PAIR && wbase + t >= wend) wl = 0.0;   // an odd run: the second half is a slice short
-        smp = gather(wbase + t + 1);
+        const int tg = kRows ? (int)(t & (kGroup - 1)) : 0;
+        if (!kRows || tg == 0) {
+            if constexpr (EXPO == EXPO_M6) wl = m6_weight(p, wr, smp);
+            else if constexpr (EXPO == EXPO_COMM) wl = comm_weight(p, wr, smp);
+            else wl = combine_weight(p, wr, smp);
+            // steps past the run (an odd half of a pair, the end of a group)
+            if (kRows && wbase + wstep + t >= wend) wl = 0.0;
+            smp = gather(t + (kRows ? kGroup : 1));
+            if constexpr (kRows) {
+                bounds = row16_sum_f(fabsf((float)wl) * beta) * (1.0f + 0x1p-18f);
+                fits = __ballot((double)bounds <= lsth);
+                wave_lds_fence();
+                lw[L.lane] = wl;
+                wave_lds_fence();
+            }
+        }
         Sq<NT> G = sq_diagonal<NT>(L, 0.0);
         auto load = [&](int m, int i, int n, double (&v)[8]) {
             const double* b = bas + m * MAT + (i * NT + n) * 512;
@@ -127,20 +157,18 @@ __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 8 : 1))) propagate
                 A.t[i][n].im[r] = fma(w, v[4 + r], A.t[i][n].im[r]);
             }
         };
-        double bound;
-        if constexpr (EXPO == EXPO_BASIS) {
-            float b;
-            {
-                const float s = row16_sum_f(fabsf((float)wl) * beta);
-                auto row = [&](int q) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), 16 * q)); };
-                b = PAIR ? fmaxf(row(0) + row(1), row(2) + row(3)) : (row(0) + row(1)) + (row(2) + row(3));
-            }
-            bound = (double)(b * (1.0f + 0x1p-18f));
+        double bound = 0.0;
+        if constexpr (kRows) {
+            // weights of this step: row tg (PAIR: rows tg and 2 + tg, by column)
+            const double* w = lw + 16 * tg + (bsecond ? 32 : 0);
             // the entries of four (D = 16) basis matrices are loaded before
             // their FMAs, so the load latencies overlap
             constexpr int B = NT == 1 ? 4 : 1;
             int m = 0;
             for (; m + B <= nb; m += B) {
+                double wv[B];
+#pragma unroll
+                for (int q = 0; q < B; ++q) wv[q] = w[m + q];
 #pragma unroll
                 for (int i = 0; i < NT; ++i) {
                     double x[B][NT][8];
@@ -149,20 +177,15 @@ __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 8 : 1))) propagate
 #pragma unroll
                         for (int n = 0; n < NT; ++n) load(m + q, i, n, x[q][n]);
 #pragma unroll
-                    for (int q = 0; q < B; ++q) {
-                        double w = readlane_d(wl, m + q);
-                        if constexpr (PAIR) w = bsecond ? readlane_d(wl, 32 + m + q) : w;
+                    for (int q = 0; q < B; ++q)
 #pragma unroll
-                        for (int n = 0; n < NT; ++n) addto(G, i, n, w, x[q][n]);
-                    }
+                        for (int n = 0; n < NT; ++n) addto(G, i, n, wv[q], x[q][n]);
                 }
             }
             for (; m < nb; ++m) {
-                double w = readlane_d(wl, m);
-                if constexpr (PAIR) w = bsecond ? readlane_d(wl, 32 + m) : w;
                 double v[8];
                 load(m, 0, 0, v);
-                addto(G, 0, 0, w, v);
+                addto(G, 0, 0, w[m], v);
             }
         } else {
             Sq<NT> P2 = G, P3 = G;
@@ -230,11 +253,24 @@ __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 8 : 1))) propagate
             scale();
             E = sq_cheb<NT, KS>(G, m, p.ctheta[m], p.cheb_j + kChebSplitOffset + m * 2 * kChebHalf, L);
         } else {
-            int q = p.force_s >= 0 ? -1 : plan_scheme(bound, lsth);
+            int q;
+            if constexpr (kRows) {
+                const unsigned a = (unsigned)(fits >> (16 * tg)) & 0xffffu;
+                const unsigned c = PAIR ? (unsigned)(fits >> (32 + 16 * tg)) & 0xffffu : a;
+                q = a && c && p.force_s < 0 ? max(__builtin_ctz(a), __builtin_ctz(c)) : -1;
+                if (q < 0) {
+                    auto of = [&](int r) {
+                        return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bounds), 16 * r));
+                    };
+                    bound = PAIR ? fmaxf(of(tg), of(2 + tg)) : of(tg);
+                }
+            } else {
+                q = p.force_s >= 0 ? -1 : plan_scheme(bound, lsth);
+            }
             if (q < 0) {
                 // squarings: the exponent's own 1-norm may be the smaller bound
                 // (terms that cancel)
-                plan_scheme_s(p, fmin(bound, sq_norm1<NT>(G)), L.lane, lsth, q, s);
+                plan_scheme_s(p, fmin(bound, sq_norm1<NT>(G)), L.lane, lane_sth_of(p, L.lane), q, s);
                 s = wave_uniform(s);
                 scale();
             }
@@ -250,16 +286,16 @@ __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 8 : 1))) propagate
             double* out = reinterpret_cast<double*>(p.slices_out);
             if constexpr (PAIR) {
                 const int64_t js = bsecond ? jm + t : j0 + t;
-                const int row = L.j & 7;
-                if (row < p.du && js < (bsecond ? j1 : jm)) {
-                    double* o = out + (js * dd + (int64_t)row * p.du) * 2;
+                const int ro = L.j & 7;
+                if (ro < p.du && js < (bsecond ? j1 : jm)) {
+                    double* o = out + (js * dd + (int64_t)ro * p.du) * 2;
 #pragma unroll
                     for (int r = 0; r < 2; ++r) {
                         const int col = L.g + 4 * r;
                         const double re = bsecond ? E.t[0][0].re[r + 2] : E.t[0][0].re[r];
                         const double im = bsecond ? E.t[0][0].im[r + 2] : E.t[0][0].im[r];
                         if (col < p.du) {
-                            o[2 * col + 0] = re + (row == col ? 1.0 : 0.0);
+                            o[2 * col + 0] = re + (ro == col ? 1.0 : 0.0);
                             o[2 * col + 1] = -im;
                         }
                     }
@@ -267,16 +303,16 @@ __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 8 : 1))) propagate
             } else {
 #pragma unroll
                 for (int n = 0; n < NT; ++n) {
-                    const int row = 16 * n + L.j;
-                    if (row < p.du) {
-                        double* o = out + ((j0 + t) * dd + (int64_t)row * p.du) * 2;
+                    const int ro = 16 * n + L.j;
+                    if (ro < p.du) {
+                        double* o = out + ((j0 + t) * dd + (int64_t)ro * p.du) * 2;
 #pragma unroll
                         for (int i = 0; i < NT; ++i)
 #pragma unroll
                             for (int r = 0; r < 4; ++r) {
                                 const int col = 16 * i + L.g + 4 * r;
                                 if (col < p.du) {
-                                    o[2 * col + 0] = E.t[i][n].re[r] + (row == col ? 1.0 : 0.0);
+                                    o[2 * col + 0] = E.t[i][n].re[r] + (ro == col ? 1.0 : 0.0);
                                     o[2 * col + 1] = -E.t[i][n].im[r];
                                 }
                             }
@@ -298,10 +334,10 @@ __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 8 : 1))) propagate
         wave_lds_fence();
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int row = L.g + 4 * r;
+            const int ro = L.g + 4 * r;
             const bool in = r < 2 && L.j < 8;
-            const double id = row == L.j ? 1.0 : 0.0;
-            const d2_t a = scr[in ? (L.j + 8) * 17 + row + 8 : 0];   // the second half's adjoint
+            const double id = ro == L.j ? 1.0 : 0.0;
+            const d2_t a = scr[in ? (L.j + 8) * 17 + ro + 8 : 0];   // the second half's adjoint
             S.t[0][0].re[r] = in ? a.x : id;
             S.t[0][0].im[r] = in ? -a.y : 0.0;
             X.t[0][0].re[r] = in ? Q.t[0][0].re[r] : id;
@@ -315,14 +351,13 @@ __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 8 : 1))) propagate
     // basis and the scratch tiles)
     sq_combine<NT, KS>(Q, team, kWaveTeams, slots, L);
     sq_tree<NT, KS>(p, blockIdx.x, Q, team, slots, tick, L);
-    (void)kScr;
 }
 
-// LDS of a launch: the basis (BL) and a scratch tile per team, or the
+// LDS of a launch: the basis (BL), a scratch tile and 64 weights per team, or the
 // handover slots of the end, whichever is larger, after a 16-byte ticket.
 template <int NT>
 constexpr size_t wave_lds_bytes(int nb, bool bl) {
-    const size_t run = (bl ? (size_t)nb * NT * NT * 4096 : 0) + (size_t)kWaveTeams * kScratchTile * 16;
+    const size_t run = (bl ? (size_t)nb * NT * NT * 4096 : 0) + (size_t)kWaveTeams * (kScratchTile * 16 + 512);
     const size_t end = (size_t)kWaveTeams * sq_slot_entries<NT>() * 16;
     return 16 + (run > end ? run : end);
 }
