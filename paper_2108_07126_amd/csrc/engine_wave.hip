@@ -11,14 +11,14 @@ hipError_t launch_wave_cheb(int D, const PropParams& p, hipStream_t stream);
 namespace {
 
 hipError_t launch_wave16(const PropParams& p, hipStream_t stream) {
-    if (p.pair) return launch_wave_one<1, 4, EXPO_BASIS, false, true, true>(p, stream);
+    if (p.pair) return launch_wave_one<Pair<2>, EXPO_BASIS, false, true>(p, stream);
     // past that only fourth order with five controls or more (21 matrices):
     // one commutator by product instead of K (K + 1) / 2 more basis matrices
     if (p.M > kWaveBasis)
-        return p.du <= 8 ? launch_wave_one<1, 2, EXPO_COMM, false, false, true>(p, stream)
-                         : launch_wave_one<1, 4, EXPO_COMM, false, false, true>(p, stream);
-    return p.du <= 12 ? launch_wave_one<1, 3, EXPO_BASIS, false, false, true>(p, stream)
-                      : launch_wave_one<1, 4, EXPO_BASIS, false, false, true>(p, stream);
+        return p.du <= 8 ? launch_wave_one<Wide<1, 2>, EXPO_COMM, false, true>(p, stream)
+                         : launch_wave_one<Wide<1, 4>, EXPO_COMM, false, true>(p, stream);
+    return p.du <= 12 ? launch_wave_one<Wide<1, 3>, EXPO_BASIS, false, true>(p, stream)
+                      : launch_wave_one<Wide<1, 4>, EXPO_BASIS, false, true>(p, stream);
 }
 
 }  // namespace

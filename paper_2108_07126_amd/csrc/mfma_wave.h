@@ -1,17 +1,24 @@
-// One-wave teams: the FP64 MFMA engine of dimensions 5..32.
+// One-wave teams: the FP64 MFMA engine of dimensions up to 32.
 //
-// One wave carries a chain and holds every D x D complex matrix, D = 16 NT, in
-// registers: NT x NT tiles of 16 x 16 in the accumulator layout of
-// v_mfma_f64_16x16x4f64 (lane 16 g + j holds rows g + 4 r, r = 0..3, of column
-// j of each tile).  Register r of tile (k, n) is the B operand of a k-slice as it
-// stands, and register r of tile (k, i) of S the A operand of S^H: a product
-// S^H X takes both operands from the lane's own registers.  So the engine
-// computes S^H X only: S X for the Hermitian factors of the series, and for
-// the chain it carries E = exp(i G) - I, whose adjoint is exp(-i G) - I:
-// Q <- Q + E^H Q.  No product touches LDS and no wave waits for another one.
+// One wave carries a chain and holds every matrix in registers, in the
+// accumulator layout of v_mfma_f64_16x16x4f64 (lane 16 g + j holds rows
+// g + 4 r, r = 0..3, of column j of a 16 x 16 tile).  Register r of tile (k, n)
+// is the B operand of a k-slice as it stands, and register r of tile (k, i) of
+// S the A operand of S^H: a product S^H X takes both operands from the lane's
+// own registers.  So the engine computes S^H X only: S X for the Hermitian
+// factors of the series, and for the chain it carries E = exp(i G) - I, whose
+// adjoint is exp(-i G) - I: Q <- Q + E^H Q.  No product touches LDS and no wave
+// waits for another one.
 //
-// KS: the k-slices (of four rows) that the embedded dimension reaches,
-// du <= 4 KS; rows and columns past them are zero in every product.
+// Shapes (a lane's entries of a matrix are numbered e = 0 .. kRegs - 1):
+//   Wide<NT, KS>  one 16 NT x 16 NT matrix, NT x NT tiles; KS the k-slices (of
+//                 four rows) that the embedded dimension reaches, du <= 4 KS
+//                 (rows and columns past them are zero in every product);
+//   Pair<KS>      two matrices of dimension <= 4 KS <= 8 that advance together,
+//                 in the diagonal 8 x 8 blocks of one tile: lanes j < 8 hold the
+//                 first, lanes j >= 8 the second, rows g + 4 e of column j & 7.
+//                 Their products are one stacked product [A_a; A_b] [B_a, B_b]
+//                 with K = 4 KS, of which each lane keeps its own block's rows.
 #pragma once
 
 #include "mfma_tiles.h"
@@ -19,103 +26,118 @@
 namespace pm {
 namespace {
 
-template <int NT>
-struct Sq {
-    Tile<double> t[NT][NT];   // [row tile][column tile]
-};
-
 struct WLane {
     int lane, g, j;
 };
 
-// f(row tile, column tile, register) over the entries a lane holds.
-template <int NT, class F>
-__device__ __forceinline__ void sq_each(F f) {
+template <int NT_, int KS_>
+struct Wide {
+    static constexpr int NT = NT_, KS = KS_, RT = (KS + 3) / 4;
+    static constexpr bool kPair = false;
+    static constexpr int kRegs = 4 * NT * NT;
+    static constexpr int at(int i, int n, int r) { return (i * NT + n) * 4 + r; }
+    static __device__ __forceinline__ int row(const WLane& L, int e) { return 16 * (e / (4 * NT)) + L.g + 4 * (e & 3); }
+    static __device__ __forceinline__ int col(const WLane& L, int e) { return 16 * (e / 4 % NT) + L.j; }
+};
+
+template <int KS_>
+struct Pair {
+    static_assert(KS_ <= 2, "blocks of 8 x 8");
+    static constexpr int NT = 1, KS = KS_;
+    static constexpr bool kPair = true;
+    static constexpr int kRegs = KS;
+    static __device__ __forceinline__ int row(const WLane& L, int e) { return L.g + 4 * e; }
+    static __device__ __forceinline__ int col(const WLane& L, int) { return L.j & 7; }
+};
+
+// A lane's entries of a matrix (of two matrices for Pair).
+template <class S>
+struct Mx {
+    double re[S::kRegs], im[S::kRegs];
+};
+
+template <class S, class F>
+__device__ __forceinline__ void mx_each(F f) {
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-        for (int n = 0; n < NT; ++n)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) f(i, n, r);
+    for (int e = 0; e < S::kRegs; ++e) f(e);
 }
 
-__device__ __forceinline__ bool sq_diag(const WLane& L, int i, int n, int r) { return i == n && L.g + 4 * r == L.j; }
+template <class S>
+__device__ __forceinline__ bool mx_diag(const WLane& L, int e) { return S::row(L, e) == S::col(L, e); }
 
-template <int NT>
-__device__ __forceinline__ Sq<NT> sq_diagonal(const WLane& L, double v) {
-    Sq<NT> s;
-    sq_each<NT>([&](int i, int n, int r) {
-        s.t[i][n].re[r] = sq_diag(L, i, n, r) ? v : 0.0;
-        s.t[i][n].im[r] = 0.0;
+template <class S>
+__device__ __forceinline__ Mx<S> mx_diagonal(const WLane& L, double v) {
+    Mx<S> m;
+    mx_each<S>([&](int e) {
+        m.re[e] = mx_diag<S>(L, e) ? v : 0.0;
+        m.im[e] = 0.0;
     });
-    return s;
+    return m;
 }
 
-template <int NT>
-__device__ __forceinline__ void sq_add(Sq<NT>& y, const Sq<NT>& x) {
-    sq_each<NT>([&](int i, int n, int r) {
-        y.t[i][n].re[r] += x.t[i][n].re[r];
-        y.t[i][n].im[r] += x.t[i][n].im[r];
+template <class S>
+__device__ __forceinline__ void mx_add(Mx<S>& y, const Mx<S>& x) {
+    mx_each<S>([&](int e) {
+        y.re[e] += x.re[e];
+        y.im[e] += x.im[e];
     });
 }
 
-// S^H X as three real products chained through the accumulator:
-// k = (Sr - Si) Xr, Re = k + Si (Xr + Xi), Im = k + Sr (Xi - Xr).  Re and Im
+// A^H X as three real products chained through the accumulator:
+// k = (Ar - Ai) Xr, Re = k + Ai (Xr + Xi), Im = k + Ar (Xi - Xr).  Re and Im
 // start from k as their MFMAs' C operand, so no sums follow the matrix
 // instructions (the usual t1 + t2, t3 - t1 + t2 take 12 more vector
 // instructions a tile, and none of those overlaps an FP64 MFMA of its SIMD).
-// STK (NT = 1): slice pairs.  The two 8 x 8 diagonal blocks hold two slices
-// and are multiplied as the stacked product [A_a; A_b] [B_a, B_b], K = 8
-// instead of 16: for k-slice s the lane (g, j) supplies its register s (its
-// column in the first block) or s + 2 (second block) of both operands.  The
-// off-diagonal blocks of the result hold cross products, which no stacked
-// product reads (pair_mask clears them before a full one).
-template <int NT, int KS, bool STK = false>
-__device__ __forceinline__ Sq<NT> sq_mul(const Sq<NT>& S, const Sq<NT>& X) {
-    Sq<NT> out;
-    if constexpr (STK) {
-        static_assert(NT == 1, "slice pairs live in one tile");
-        const bool hi = (__lane_id() & 8) != 0;
-        const Tile<double>&A = S.t[0][0], &B = X.t[0][0];
-        double sr[2], si[2], xr[2], xi[2];
+// The operands' sums come ahead of the MFMAs: one right before the MFMA that
+// reads it would cost wait states each time.
+template <class S>
+__device__ __forceinline__ Mx<S> mx_mul(const Mx<S>& A, const Mx<S>& X) {
+    Mx<S> out;
+    constexpr int KS = S::KS;
+    if constexpr (S::kPair) {
+        double sd[KS], xp[KS], xm[KS];
+#pragma unroll
+        for (int q = 0; q < KS; ++q) {
+            sd[q] = A.re[q] - A.im[q];
+            xp[q] = X.re[q] + X.im[q];
+            xm[q] = X.im[q] - X.re[q];
+        }
+        __builtin_amdgcn_sched_barrier(0);
         d4_t kk = {0, 0, 0, 0};
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            sr[q] = hi ? A.re[q + 2] : A.re[q];
-            si[q] = hi ? A.im[q + 2] : A.im[q];
-            xr[q] = hi ? B.re[q + 2] : B.re[q];
-            xi[q] = hi ? B.im[q + 2] : B.im[q];
-            kk = mfma16(sr[q] - si[q], xr[q], kk);
-        }
+        for (int q = 0; q < KS; ++q) kk = mfma16(sd[q], X.re[q], kk);
         d4_t re = kk, im = kk;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            re = mfma16(si[q], xr[q] + xi[q], re);
-            im = mfma16(sr[q], xi[q] - xr[q], im);
+        for (int q = 0; q < KS; ++q) {
+            re = mfma16(A.im[q], xp[q], re);
+            im = mfma16(A.re[q], xm[q], im);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        // rows of the lane's own block (the others hold cross products)
+        const bool hi = (__lane_id() & 8) != 0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            out.t[0][0].re[r] = re[r];
-            out.t[0][0].im[r] = im[r];
+        for (int q = 0; q < KS; ++q) {
+            out.re[q] = hi ? re[q + 2] : re[q];
+            out.im[q] = hi ? im[q + 2] : im[q];
         }
-        return out;
     } else {
-        constexpr int RT = (KS + 3) / 4;
-        // the operands' sums ahead of the MFMAs (one right before the MFMA
-        // that reads it would cost wait states each time)
-        double sd[NT][KS];
+        constexpr int NT = S::NT, RT = S::RT;
+        double sd[RT][KS];
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
-            for (int q = 0; q < KS; ++q) sd[i][q] = S.t[q >> 2][i].re[q & 3] - S.t[q >> 2][i].im[q & 3];
+            for (int q = 0; q < KS; ++q) {
+                const int e = S::at(q >> 2, i, q & 3);
+                sd[i][q] = A.re[e] - A.im[e];
+            }
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
             double xp[KS], xm[KS];
 #pragma unroll
             for (int q = 0; q < KS; ++q) {
-                const Tile<double>& B = X.t[q >> 2][n];
-                xp[q] = B.re[q & 3] + B.im[q & 3];
-                xm[q] = B.im[q & 3] - B.re[q & 3];
+                const int e = S::at(q >> 2, n, q & 3);
+                xp[q] = X.re[e] + X.im[e];
+                xm[q] = X.im[e] - X.re[e];
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -123,27 +145,35 @@ __device__ __forceinline__ Sq<NT> sq_mul(const Sq<NT>& S, const Sq<NT>& X) {
                 d4_t kk = {0, 0, 0, 0};
                 if (i < RT && n < RT) {
 #pragma unroll
-                    for (int q = 0; q < KS; ++q) kk = mfma16(sd[i][q], X.t[q >> 2][n].re[q & 3], kk);
+                    for (int q = 0; q < KS; ++q) kk = mfma16(sd[i][q], X.re[S::at(q >> 2, n, q & 3)], kk);
                 }
                 d4_t re = kk, im = kk;
                 if (i < RT && n < RT) {
 #pragma unroll
                     for (int q = 0; q < KS; ++q) {
-                        const Tile<double>& A = S.t[q >> 2][i];
-                        re = mfma16(A.im[q & 3], xp[q], re);
-                        im = mfma16(A.re[q & 3], xm[q], im);
+                        const int e = S::at(q >> 2, i, q & 3);
+                        re = mfma16(A.im[e], xp[q], re);
+                        im = mfma16(A.re[e], xm[q], im);
                     }
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    out.t[i][n].re[r] = re[r];
-                    out.t[i][n].im[r] = im[r];
+                    out.re[S::at(i, n, r)] = re[r];
+                    out.im[S::at(i, n, r)] = im[r];
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        return out;
     }
+    return out;
+}
+
+// X + A^H X.
+template <class S>
+__device__ __forceinline__ Mx<S> mx_apply(const Mx<S>& A, const Mx<S>& X) {
+    Mx<S> y = mx_mul<S>(A, X);
+    mx_add<S>(y, X);
+    return y;
 }
 
 // exp(i G) - I for the (pre-scaled) Hermitian G by evaluation scheme q
@@ -153,22 +183,22 @@ __device__ __forceinline__ Sq<NT> sq_mul(const Sq<NT>& S, const Sq<NT>& X) {
 //   q >= 3 blocks B_i = c_{3i} + c_{3i+1} i G - c_{3i+2} Y over powers of
 //          (i G)^3 = -i Z, X <- B_i - i Z X: q products in all.
 // Every left factor is Hermitian.
-template <int NT, int KS, bool STK>
-__device__ __forceinline__ Sq<NT> sq_expm1(const PropParams& p, const Sq<NT>& G, int q, const WLane& L) {
-    Sq<NT> E;
+template <class S>
+__device__ __forceinline__ Mx<S> mx_expm1(const PropParams& p, const Mx<S>& G, int q, const WLane& L) {
+    Mx<S> E;
     if (q == 0) {
-        sq_each<NT>([&](int i, int n, int r) {
-            E.t[i][n].re[r] = -G.t[i][n].im[r];
-            E.t[i][n].im[r] = G.t[i][n].re[r];
+        mx_each<S>([&](int e) {
+            E.re[e] = -G.im[e];
+            E.im[e] = G.re[e];
         });
         return E;
     }
-    const Sq<NT> Y = sq_mul<NT, KS, STK>(G, G);
+    const Mx<S> Y = mx_mul<S>(G, G);
     // c0 I + c1 i G - c2 Y into E
     auto block = [&](double c0, double c1, double c2) {
-        sq_each<NT>([&](int i, int n, int r) {
-            E.t[i][n].re[r] = fma(-c1, G.t[i][n].im[r], fma(-c2, Y.t[i][n].re[r], sq_diag(L, i, n, r) ? c0 : 0.0));
-            E.t[i][n].im[r] = fma(c1, G.t[i][n].re[r], -c2 * Y.t[i][n].im[r]);
+        mx_each<S>([&](int e) {
+            E.re[e] = fma(-c1, G.im[e], fma(-c2, Y.re[e], mx_diag<S>(L, e) ? c0 : 0.0));
+            E.im[e] = fma(c1, G.re[e], -c2 * Y.im[e]);
         });
     };
     if (q <= 2) {
@@ -177,73 +207,80 @@ __device__ __forceinline__ Sq<NT> sq_expm1(const PropParams& p, const Sq<NT>& G,
             return E;
         }
         block(p.tc[2], p.tc[3], p.tc[4]);
-        E = sq_mul<NT, KS, STK>(Y, E);
-        sq_each<NT>([&](int i, int n, int r) {
-            E.t[i][n].re[r] = -G.t[i][n].im[r] - E.t[i][n].re[r];
-            E.t[i][n].im[r] = G.t[i][n].re[r] - E.t[i][n].im[r];
+        E = mx_mul<S>(Y, E);
+        mx_each<S>([&](int e) {
+            E.re[e] = -G.im[e] - E.re[e];
+            E.im[e] = G.re[e] - E.im[e];
         });
         return E;
     }
     int b = q - 2;   // the leading block
-    const Sq<NT> Z = sq_mul<NT, KS, STK>(G, Y);
+    const Mx<S> Z = mx_mul<S>(G, Y);
     block(p.tc[3 * b], p.tc[3 * b + 1], p.tc[3 * b + 2]);
     const double c3 = p.tc[3 * b + 3];
-    sq_each<NT>([&](int i, int n, int r) {
-        E.t[i][n].re[r] = fma(c3, Z.t[i][n].im[r], E.t[i][n].re[r]);
-        E.t[i][n].im[r] = fma(-c3, Z.t[i][n].re[r], E.t[i][n].im[r]);
+    mx_each<S>([&](int e) {
+        E.re[e] = fma(c3, Z.im[e], E.re[e]);
+        E.im[e] = fma(-c3, Z.re[e], E.im[e]);
     });
     while (--b > 0) {
-        const Sq<NT> W = sq_mul<NT, KS, STK>(Z, E);
+        const Mx<S> W = mx_mul<S>(Z, E);
         block(p.tc[3 * b], p.tc[3 * b + 1], p.tc[3 * b + 2]);
-        sq_each<NT>([&](int i, int n, int r) {
-            E.t[i][n].re[r] += W.t[i][n].im[r];
-            E.t[i][n].im[r] -= W.t[i][n].re[r];
+        mx_each<S>([&](int e) {
+            E.re[e] += W.im[e];
+            E.im[e] -= W.re[e];
         });
     }
     // the last block: c0 left out, c1 = 1
-    const Sq<NT> W = sq_mul<NT, KS, STK>(Z, E);
+    const Mx<S> W = mx_mul<S>(Z, E);
     const double c2 = p.tc[2];
-    sq_each<NT>([&](int i, int n, int r) {
-        E.t[i][n].re[r] = fma(-c2, Y.t[i][n].re[r], W.t[i][n].im[r]) - G.t[i][n].im[r];
-        E.t[i][n].im[r] = fma(-c2, Y.t[i][n].im[r], G.t[i][n].re[r]) - W.t[i][n].re[r];
+    mx_each<S>([&](int e) {
+        E.re[e] = fma(-c2, Y.re[e], W.im[e]) - G.im[e];
+        E.im[e] = fma(-c2, Y.im[e], G.re[e]) - W.re[e];
     });
     return E;
 }
 
-// exp(i G) - I by the degree-m Chebyshev series of cheb_parts on the interval
-// [-theta, theta]: C + i P with C = sum e_i T_i(Y) and P = X sum b_i T_i(Y),
-// X = G / theta, Y = 2 X^2 - I; `ec` the degree's row of even and odd
-// coefficients.
-template <int NT, int KS>
-__device__ __forceinline__ Sq<NT> sq_cheb(const Sq<NT>& G, int m, double theta, const double* ec, const WLane& L) {
+// exp(i G) - I by the degree-m Chebyshev series on the interval
+// [-theta, theta], the spectrum's bound (eq. chebychev_series with
+// alpha = -theta, beta = theta), split into its even and odd halves.  With
+// X = G / theta and Y = T_2(X) = 2 X^2 - I, T_2j(X) = T_j(Y) and
+// T_{2j+1}(X) = X (2 sum_{i=1..j} (-1)^{j-i} T_i(Y) + (-1)^j I), so
+//   exp(i G) = C + i P,  C = sum_{i <= m/2} e_i T_i(Y),
+//   P = X sum_{i <= (m-1)/2} b_i T_i(Y),
+// e_0 = J_0, e_i = 2 (-1)^i J_2i, and b the alternating suffix sums of the
+// odd coefficients (`ec`: the degree's row of e, then of b, kChebHalf each).
+// floor(m/2) + 1 products, all with a Hermitian left factor, where the
+// Clenshaw recurrence in X takes m.
+template <class S>
+__device__ __forceinline__ Mx<S> mx_cheb(const Mx<S>& G, int m, double theta, const double* ec, const WLane& L) {
     const double inv = 1.0 / theta;
     const double* eb = ec + kChebHalf;
     const int qc = m / 2, qs = (m - 1) / 2;
-    Sq<NT> X, C = sq_diagonal<NT>(L, ec[0]), Sp = sq_diagonal<NT>(L, eb[0]);
-    sq_each<NT>([&](int i, int n, int r) {
-        X.t[i][n].re[r] = G.t[i][n].re[r] * inv;
-        X.t[i][n].im[r] = G.t[i][n].im[r] * inv;
+    Mx<S> X, C = mx_diagonal<S>(L, ec[0]), Sp = mx_diagonal<S>(L, eb[0]);
+    mx_each<S>([&](int e) {
+        X.re[e] = G.re[e] * inv;
+        X.im[e] = G.im[e] * inv;
     });
-    auto add = [&](Sq<NT>& A, double c, const Sq<NT>& B) {
-        sq_each<NT>([&](int i, int n, int r) {
-            A.t[i][n].re[r] = fma(c, B.t[i][n].re[r], A.t[i][n].re[r]);
-            A.t[i][n].im[r] = fma(c, B.t[i][n].im[r], A.t[i][n].im[r]);
+    auto add = [&](Mx<S>& A, double c, const Mx<S>& B) {
+        mx_each<S>([&](int e) {
+            A.re[e] = fma(c, B.re[e], A.re[e]);
+            A.im[e] = fma(c, B.im[e], A.im[e]);
         });
     };
     if (qc >= 1) {
-        Sq<NT> Y = sq_mul<NT, KS>(X, X), Tm = sq_diagonal<NT>(L, 1.0);
-        sq_each<NT>([&](int i, int n, int r) {
-            Y.t[i][n].re[r] = fma(2.0, Y.t[i][n].re[r], -Tm.t[i][n].re[r]);
-            Y.t[i][n].im[r] *= 2.0;
+        Mx<S> Y = mx_mul<S>(X, X), Tm = mx_diagonal<S>(L, 1.0);
+        mx_each<S>([&](int e) {
+            Y.re[e] = fma(2.0, Y.re[e], -Tm.re[e]);
+            Y.im[e] *= 2.0;
         });
         add(C, ec[1], Y);
         if (qs >= 1) add(Sp, eb[1], Y);
-        Sq<NT> Tc = Y;
+        Mx<S> Tc = Y;
         for (int i = 2; i <= qc; ++i) {
-            Sq<NT> Tn = sq_mul<NT, KS>(Y, Tc);
-            sq_each<NT>([&](int a, int n, int r) {
-                Tn.t[a][n].re[r] = fma(2.0, Tn.t[a][n].re[r], -Tm.t[a][n].re[r]);
-                Tn.t[a][n].im[r] = fma(2.0, Tn.t[a][n].im[r], -Tm.t[a][n].im[r]);
+            Mx<S> Tn = mx_mul<S>(Y, Tc);
+            mx_each<S>([&](int e) {
+                Tn.re[e] = fma(2.0, Tn.re[e], -Tm.re[e]);
+                Tn.im[e] = fma(2.0, Tn.im[e], -Tm.im[e]);
             });
             add(C, ec[i], Tn);
             if (i <= qs) add(Sp, eb[i], Tn);
@@ -251,18 +288,18 @@ __device__ __forceinline__ Sq<NT> sq_cheb(const Sq<NT>& G, int m, double theta, 
             Tc = Tn;
         }
     }
-    Sq<NT> P;
+    Mx<S> P;
     if (qs >= 1) {
-        P = sq_mul<NT, KS>(X, Sp);
+        P = mx_mul<S>(X, Sp);
     } else {
-        sq_each<NT>([&](int i, int n, int r) {
-            P.t[i][n].re[r] = eb[0] * X.t[i][n].re[r];
-            P.t[i][n].im[r] = eb[0] * X.t[i][n].im[r];
+        mx_each<S>([&](int e) {
+            P.re[e] = eb[0] * X.re[e];
+            P.im[e] = eb[0] * X.im[e];
         });
     }
-    sq_each<NT>([&](int i, int n, int r) {
-        C.t[i][n].re[r] = (C.t[i][n].re[r] - (sq_diag(L, i, n, r) ? 1.0 : 0.0)) - P.t[i][n].im[r];
-        C.t[i][n].im[r] += P.t[i][n].re[r];
+    mx_each<S>([&](int e) {
+        C.re[e] = (C.re[e] - (mx_diag<S>(L, e) ? 1.0 : 0.0)) - P.im[e];
+        C.im[e] += P.re[e];
     });
     return C;
 }
@@ -277,116 +314,152 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// The adjoint of a matrix, tile by tile through a 16 x 17 scratch tile of the
-// wave (row stride 17 entries: rows and columns both read without conflicts).
+// The adjoint of a matrix through the wave's scratch tile: tiles one by one
+// with a row stride of 17 entries (8 x 8 blocks: 9), so that rows and columns
+// are both accessed without conflicts.
 constexpr int kScratchTile = 16 * 17;   // d2_t entries
-template <int NT>
-__device__ __forceinline__ Sq<NT> sq_adjoint(const Sq<NT>& X, d2_t* scr, const WLane& L) {
-    Sq<NT> o;
+template <class S>
+__device__ __forceinline__ Mx<S> mx_adjoint(const Mx<S>& X, d2_t* scr, const WLane& L) {
+    Mx<S> o;
+    if constexpr (S::kPair) {
+        d2_t* b = scr + (L.j >> 3) * 72;
+        const int c = L.j & 7;
+        wave_lds_fence();
+        mx_each<S>([&](int e) { b[(L.g + 4 * e) * 9 + c] = d2_t{X.re[e], X.im[e]}; });
+        wave_lds_fence();
+        mx_each<S>([&](int e) {
+            // (with KS = 1 nothing was written to rows 4 and on)
+            const d2_t v = b[(S::KS == 1 ? c & 3 : c) * 9 + L.g + 4 * e];
+            const bool in = S::KS > 1 || c < 4;
+            o.re[e] = in ? v.x : 0.0;
+            o.im[e] = in ? -v.y : 0.0;
+        });
+    } else {
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+        for (int i = 0; i < S::NT; ++i)
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            wave_lds_fence();
+            for (int n = 0; n < S::NT; ++n) {
+                wave_lds_fence();
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                scr[(L.g + 4 * r) * 17 + L.j] = d2_t{X.t[n][i].re[r], X.t[n][i].im[r]};
-            wave_lds_fence();
+                for (int r = 0; r < 4; ++r)
+                    scr[(L.g + 4 * r) * 17 + L.j] = d2_t{X.re[S::at(n, i, r)], X.im[S::at(n, i, r)]};
+                wave_lds_fence();
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const d2_t v = scr[L.j * 17 + L.g + 4 * r];
-                o.t[i][n].re[r] = v.x;
-                o.t[i][n].im[r] = -v.y;
+                for (int r = 0; r < 4; ++r) {
+                    const d2_t v = scr[L.j * 17 + L.g + 4 * r];
+                    o.re[S::at(i, n, r)] = v.x;
+                    o.im[S::at(i, n, r)] = -v.y;
+                }
             }
-        }
+    }
     return o;
 }
 
 // [X, Y] = X Y - (X Y)^H of Hermitian X, Y.
-template <int NT, int KS>
-__device__ __forceinline__ Sq<NT> sq_commutator(const Sq<NT>& X, const Sq<NT>& Y, d2_t* scr, const WLane& L) {
-    Sq<NT> Z = sq_mul<NT, KS>(X, Y);
-    const Sq<NT> A = sq_adjoint<NT>(Z, scr, L);
-    sq_each<NT>([&](int i, int n, int r) {
-        Z.t[i][n].re[r] -= A.t[i][n].re[r];
-        Z.t[i][n].im[r] -= A.t[i][n].im[r];
+template <class S>
+__device__ __forceinline__ Mx<S> mx_commutator(const Mx<S>& X, const Mx<S>& Y, d2_t* scr, const WLane& L) {
+    Mx<S> Z = mx_mul<S>(X, Y);
+    const Mx<S> A = mx_adjoint<S>(Z, scr, L);
+    mx_each<S>([&](int e) {
+        Z.re[e] -= A.re[e];
+        Z.im[e] -= A.im[e];
     });
     return Z;
 }
 
 // E <- (I + E)^2 - I = 2 E + E E, s times.
-template <int NT, int KS>
-__device__ __forceinline__ void sq_square(Sq<NT>& E, int s, d2_t* scr, const WLane& L) {
+template <class S>
+__device__ __forceinline__ void mx_square(Mx<S>& E, int s, d2_t* scr, const WLane& L) {
     for (int q = 0; q < s; ++q) {
-        const Sq<NT> P = sq_mul<NT, KS>(sq_adjoint<NT>(E, scr, L), E);
-        sq_each<NT>([&](int i, int n, int r) {
-            E.t[i][n].re[r] = fma(2.0, E.t[i][n].re[r], P.t[i][n].re[r]);
-            E.t[i][n].im[r] = fma(2.0, E.t[i][n].im[r], P.t[i][n].im[r]);
+        const Mx<S> P = mx_mul<S>(mx_adjoint<S>(E, scr, L), E);
+        mx_each<S>([&](int e) {
+            E.re[e] = fma(2.0, E.re[e], P.re[e]);
+            E.im[e] = fma(2.0, E.im[e], P.im[e]);
         });
     }
 }
 
-// ||G||_1 (bound) of the Hermitian G as its largest row sum.
-template <int NT>
-__device__ __forceinline__ double sq_norm1(const Sq<NT>& G) {
+// ||G||_1 (bound) of the Hermitian G as its largest row sum (Pair: over both).
+template <class S>
+__device__ __forceinline__ double mx_norm1(const Mx<S>& G) {
     float m = 0.0f;
+    if constexpr (S::kPair) {
+        mx_each<S>([&](int e) {
+            float s = abs_bound_f(G.re[e], G.im[e]);
+            s += __shfl_xor(s, 1);
+            s += __shfl_xor(s, 2);
+            s += __shfl_xor(s, 4);
+            m = fmaxf(m, fmaxf(s, __shfl_xor(s, 8)));
+        });
+    } else {
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+        for (int i = 0; i < S::NT; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float s = 0.0f;
+            for (int r = 0; r < 4; ++r) {
+                float s = 0.0f;
 #pragma unroll
-            for (int n = 0; n < NT; ++n) s += abs_bound_f(G.t[i][n].re[r], G.t[i][n].im[r]);
-            m = fmaxf(m, row16_sum_f(s));
-        }
+                for (int n = 0; n < S::NT; ++n) s += abs_bound_f(G.re[S::at(i, n, r)], G.im[S::at(i, n, r)]);
+                m = fmaxf(m, row16_sum_f(s));
+            }
+    }
     return rows_max_f(m);
 }
 
 // Node (chain or tree product) in memory: [D][D] complex128, row-major.
-template <int NT>
-__device__ __forceinline__ void sq_node_store(double* node, const Sq<NT>& Q, const WLane& L) {
+template <class S>
+__device__ __forceinline__ void mx_node_store(double* node, const Mx<S>& Q, const WLane& L) {
     d2_t* o = reinterpret_cast<d2_t*>(node);
-    sq_each<NT>([&](int i, int n, int r) {
-        o[(16 * i + L.g + 4 * r) * (16 * NT) + 16 * n + L.j] = d2_t{Q.t[i][n].re[r], Q.t[i][n].im[r]};
+    mx_each<S>([&](int e) { o[S::row(L, e) * (16 * S::NT) + S::col(L, e)] = d2_t{Q.re[e], Q.im[e]}; });
+}
+
+// A node of an earlier launch, or with ADJ its adjoint (a left factor).
+template <class S, bool ADJ>
+__device__ __forceinline__ Mx<S> mx_node_load(const double* node, const WLane& L) {
+    const d2_t* o = reinterpret_cast<const d2_t*>(node);
+    Mx<S> Q;
+    mx_each<S>([&](int e) {
+        const d2_t v = o[ADJ ? S::col(L, e) * (16 * S::NT) + S::row(L, e) : S::row(L, e) * (16 * S::NT) + S::col(L, e)];
+        Q.re[e] = v.x;
+        Q.im[e] = ADJ ? -v.y : v.y;
     });
+    return Q;
 }
 
 // Nodes shared inside the launch travel as agent-scope atomic accesses
 // (node_store_coherent: why no fences are needed).
-template <int NT>
-__device__ __forceinline__ void sq_node_publish(double* node, const Sq<NT>& Q, const WLane& L) {
-    sq_each<NT>([&](int i, int n, int r) {
-        double* o = node + ((16 * i + L.g + 4 * r) * (16 * NT) + 16 * n + L.j) * 2;
-        __hip_atomic_store(o, Q.t[i][n].re[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(o + 1, Q.t[i][n].im[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+template <class S>
+__device__ __forceinline__ void mx_node_publish(double* node, const Mx<S>& Q, const WLane& L) {
+    mx_each<S>([&](int e) {
+        double* o = node + (S::row(L, e) * (16 * S::NT) + S::col(L, e)) * 2;
+        __hip_atomic_store(o, Q.re[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(o + 1, Q.im[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     });
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0);
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
-// A published node, or with ADJ its adjoint (the left factor of a product).
-template <int NT, bool ADJ>
-__device__ __forceinline__ Sq<NT> sq_node_fetch(double* node, const WLane& L) {
-    Sq<NT> Q;
-    sq_each<NT>([&](int i, int n, int r) {
-        const int row = 16 * i + L.g + 4 * r, col = 16 * n + L.j;
-        double* o = node + (ADJ ? col * (16 * NT) + row : row * (16 * NT) + col) * 2;
-        Q.t[i][n].re[r] = __hip_atomic_load(o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        Q.t[i][n].im[r] = __hip_atomic_load(o + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (ADJ) Q.t[i][n].im[r] = -Q.t[i][n].im[r];
+template <class S, bool ADJ>
+__device__ __forceinline__ Mx<S> mx_node_fetch(double* node, const WLane& L) {
+    Mx<S> Q;
+    mx_each<S>([&](int e) {
+        const int row = S::row(L, e), col = S::col(L, e);
+        double* o = node + (ADJ ? col * (16 * S::NT) + row : row * (16 * S::NT) + col) * 2;
+        Q.re[e] = __hip_atomic_load(o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        Q.im[e] = __hip_atomic_load(o + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (ADJ) Q.im[e] = -Q.im[e];
     });
     return Q;
 }
 
 // Root product into U_out.
-template <int NT>
-__device__ __forceinline__ void sq_store_root(const PropParams& p, const Sq<NT>& Q, const WLane& L) {
-    sq_each<NT>([&](int i, int n, int r) {
-        const int row = 16 * i + L.g + 4 * r, col = 16 * n + L.j;
+template <class S>
+__device__ __forceinline__ void mx_store_root(const PropParams& p, const Mx<S>& Q, const WLane& L) {
+    mx_each<S>([&](int e) {
+        const int row = S::row(L, e), col = S::col(L, e);
         if (row < p.du && col < p.du) {
-            p.U_out[(row * p.du + col) * 2 + 0] = Q.t[i][n].re[r];
-            p.U_out[(row * p.du + col) * 2 + 1] = Q.t[i][n].im[r];
+            p.U_out[(row * p.du + col) * 2 + 0] = Q.re[e];
+            p.U_out[(row * p.du + col) * 2 + 1] = Q.im[e];
         }
     });
 }
@@ -397,30 +470,28 @@ __device__ __forceinline__ void sq_store_root(const PropParams& p, const Sq<NT>&
 // four of D (D + 1) entries; the handed matrix is written by rows and read as
 // its adjoint, both without bank conflicts.
 constexpr int kWaveTeams = 4;
-template <int NT>
-constexpr int sq_slot_entries() { return 16 * NT * (16 * NT + 1); }
+template <class S>
+constexpr int mx_slot_entries() { return 16 * S::NT * (16 * S::NT + 1); }
 
-template <int NT, int KS>
-__device__ __forceinline__ void sq_combine(Sq<NT>& Q, int team, int live, d2_t* slots, const WLane& L) {
-    constexpr int LD = 16 * NT + 1;
-    d2_t* own = slots + team * sq_slot_entries<NT>();
+template <class S>
+__device__ __forceinline__ void mx_combine(Mx<S>& Q, int team, int live, d2_t* slots, const WLane& L) {
+    constexpr int LD = 16 * S::NT + 1;
+    d2_t* own = slots + team * mx_slot_entries<S>();
 #pragma unroll
     for (int st = 1; st < kWaveTeams; st <<= 1) {
         __syncthreads();
         if ((team & (2 * st - 1)) == st && team < live)
-            sq_each<NT>([&](int i, int n, int r) {
-                own[(16 * i + L.g + 4 * r) * LD + 16 * n + L.j] = d2_t{Q.t[i][n].re[r], Q.t[i][n].im[r]};
-            });
+            mx_each<S>([&](int e) { own[S::row(L, e) * LD + S::col(L, e)] = d2_t{Q.re[e], Q.im[e]}; });
         __syncthreads();
         if ((team & (2 * st - 1)) == 0 && team + st < live) {
-            const d2_t* later = slots + (team + st) * sq_slot_entries<NT>();
-            Sq<NT> S;
-            sq_each<NT>([&](int i, int n, int r) {
-                const d2_t v = later[(16 * n + L.j) * LD + 16 * i + L.g + 4 * r];
-                S.t[i][n].re[r] = v.x;
-                S.t[i][n].im[r] = -v.y;
+            const d2_t* later = slots + (team + st) * mx_slot_entries<S>();
+            Mx<S> A;
+            mx_each<S>([&](int e) {
+                const d2_t v = later[S::col(L, e) * LD + S::row(L, e)];
+                A.re[e] = v.x;
+                A.im[e] = -v.y;
             });
-            Q = sq_mul<NT, KS>(S, Q);
+            Q = mx_mul<S>(A, Q);
         }
     }
 }
@@ -428,23 +499,23 @@ __device__ __forceinline__ void sq_combine(Sq<NT>& Q, int team, int live, d2_t* 
 // The ticketed product tree (fan-in kFanIn) of blocks of four one-wave teams,
 // which stay together into it: team 0 publishes the block's node and takes
 // its group's ticket; in the group's last arrival team w multiplies nodes
-// 2 w + 1 and 2 w, read straight from memory, and sq_combine does the rest:
+// 2 w + 1 and 2 w, read straight from memory, and mx_combine does the rest:
 // three dependent products per level.
-template <int NT, int KS>
-__device__ void sq_tree(const PropParams& p, int64_t leaf, Sq<NT>& Q, int team, d2_t* slots, int* tick,
+template <class S>
+__device__ void mx_tree(const PropParams& p, int64_t leaf, Mx<S>& Q, int team, d2_t* slots, int* tick,
                         const WLane& L) {
-    static_assert(2 * kWaveTeams == kFanIn, "two nodes per team");
-    constexpr int64_t NN = (int64_t)256 * NT * NT * 2;
+    static_assert(2 * kWaveTeams == kFanIn && !S::kPair, "two nodes per team");
+    constexpr int64_t NN = (int64_t)256 * S::NT * S::NT * 2;
     int64_t idx = leaf, cnt = p.n_leaves, off = 0;
     while (cnt > 1) {
         const int64_t pcnt = (cnt + kFanIn - 1) / kFanIn, poff = off + cnt, grp = idx / kFanIn;
         const int64_t first = grp * kFanIn;
         const int members = (int)(min(cnt, first + kFanIn) - first);
         if (members == 1) {
-            if (p.store_nodes && team == 0) sq_node_store<NT>(p.nodes + (off + idx) * NN, Q, L);
+            if (p.store_nodes && team == 0) mx_node_store<S>(p.nodes + (off + idx) * NN, Q, L);
         } else {
             if (team == 0) {
-                sq_node_publish<NT>(p.nodes + (off + idx) * NN, Q, L);
+                mx_node_publish<S>(p.nodes + (off + idx) * NN, Q, L);
                 unsigned v = 0;
                 if (L.lane == 0) v = atomicAdd(&p.counters[poff + grp], 1u);
                 const unsigned t = (unsigned)__builtin_amdgcn_readfirstlane((int)v);
@@ -457,20 +528,20 @@ __device__ void sq_tree(const PropParams& p, int64_t leaf, Sq<NT>& Q, int team, 
             if (t != members - 1) return;   // the whole block leaves
             double* nd = p.nodes + (off + first + 2 * team) * NN;
             if (2 * team + 1 < members) {
-                const Sq<NT> S = sq_node_fetch<NT, true>(nd + NN, L);
-                Q = sq_mul<NT, KS>(S, sq_node_fetch<NT, false>(nd, L));
+                const Mx<S> A = mx_node_fetch<S, true>(nd + NN, L);
+                Q = mx_mul<S>(A, mx_node_fetch<S, false>(nd, L));
             } else if (2 * team < members) {
-                Q = sq_node_fetch<NT, false>(nd, L);
+                Q = mx_node_fetch<S, false>(nd, L);
             }
-            sq_combine<NT, KS>(Q, team, (members + 1) / 2, slots, L);
+            mx_combine<S>(Q, team, (members + 1) / 2, slots, L);
         }
         idx = grp;
         off = poff;
         cnt = pcnt;
     }
     if (team != 0) return;
-    if (p.store_nodes) sq_node_store<NT>(p.nodes + off * NN, Q, L);
-    sq_store_root<NT>(p, Q, L);
+    if (p.store_nodes) mx_node_store<S>(p.nodes + off * NN, Q, L);
+    mx_store_root<S>(p, Q, L);
 }
 
 }  // namespace

@@ -226,6 +226,25 @@ void fill_schemes(pm::PropParams& p, int precision, int64_t n, int max_degree) {
     }
 }
 
+// The adjoint's series (adjoint_kernel.h): adth[n] is the largest ||K|| whose
+// terms past n + 1 stay below a quarter of the FP64 rounding of ||Omega||;
+// past ||K|| = 2 terms grow well above the result and the kernel doubles.
+void fill_adjoint(pm::GradParams& gp) {
+    static const struct Table {
+        double th[pm::kAdjointTerms], inv[pm::kAdjointTerms + 2];
+        Table() {
+            for (int n = 0; n < pm::kAdjointTerms; ++n) {
+                th[n] = taylor_theta(n + 1, std::ldexp(1.0, -55), false);
+                if (th[n] > 2.0) th[n] = n > 0 && th[n - 1] >= 2.0 ? -1.0 : 2.0;
+            }
+            inv[0] = 0.0;
+            for (int k = 1; k < pm::kAdjointTerms + 2; ++k) inv[k] = 1.0 / k;
+        }
+    } t;
+    std::memcpy(gp.adth, t.th, sizeof(gp.adth));
+    std::memcpy(gp.inv, t.inv, sizeof(gp.inv));
+}
+
 // Lubich's estimate of the Chebyshev truncation error (eq. error_chebychev)
 // for degree m and spectral width w = beta - alpha.
 double lubich_error(int m, double w) {
@@ -329,40 +348,45 @@ double norm1(const Mat& a, int64_t d) {
     return best;
 }
 
-// Upper bound of ||A||_2 of a Hermitian A: (||A^n||_F)^(1/n), n = 2^k by
-// repeated squaring of the scaled matrix (within d^(1/2n) of the 2-norm:
-// n = 64 2 % at d = 16, n = 16 14 % at d = 64), never above ||A||_1.
+// Upper bound of ||A||_2 of a Hermitian A: (||A^n||_F)^(1/n), n = 16 (8 past 32
+// levels) by repeated squaring of the scaled matrix, never above ||A||_1.  It
+// is within d^(1/2n) of the 2-norm (9 % at d = 16, 30 % at d = 64, a third of
+// that for a GUE matrix).  Real and imaginary planes, so the inner loop is a
+// plain vector update.
 float norm2_bound(const Mat& a, int64_t d) {
     const double n1 = norm1(a, d);
     if (!(n1 > 0.0)) return 0.0f;
-    const int squarings = d <= 16 ? 6 : (d <= 32 ? 5 : 4);
-    std::vector<double> x((size_t)(2 * d * d)), y(x.size());
+    const int squarings = d <= 32 ? 4 : 3;
+    std::vector<double> xr((size_t)(d * d)), xi(xr.size()), yr(xr.size()), yi(xr.size());
     for (int64_t i = 0; i < d * d; ++i) {
-        x[2 * i] = a[i].real() / n1;
-        x[2 * i + 1] = a[i].imag() / n1;
+        xr[i] = a[i].real() / n1;
+        xi[i] = a[i].imag() / n1;
     }
-    double lg = 0.0;   // log of the scale taken out of A^n / n1^n
+    double lg = 0.0;   // log ||A^n / n1^n||_F
     for (int k = 0; k < squarings; ++k) {
-        // A A = A A^H: entry (i, j) from rows i and j
         double f = 0.0;
-        for (int64_t i = 0; i < d; ++i)
-            for (int64_t j = i; j < d; ++j) {
-                const double *u = &x[2 * i * d], *v = &x[2 * j * d];
-                double re = 0.0, im = 0.0;
-                for (int64_t q = 0; q < d; ++q) {
-                    re += u[2 * q] * v[2 * q] + u[2 * q + 1] * v[2 * q + 1];
-                    im += u[2 * q + 1] * v[2 * q] - u[2 * q] * v[2 * q + 1];
+        for (int64_t i = 0; i < d; ++i) {
+            double *rr = &yr[i * d], *ri = &yi[i * d];
+            std::fill(rr, rr + d, 0.0);
+            std::fill(ri, ri + d, 0.0);
+            for (int64_t q = 0; q < d; ++q) {
+                const double ar = xr[i * d + q], ai = xi[i * d + q];
+                const double *br = &xr[q * d], *bi = &xi[q * d];
+                for (int64_t j = 0; j < d; ++j) {
+                    rr[j] += ar * br[j] - ai * bi[j];
+                    ri[j] += ar * bi[j] + ai * br[j];
                 }
-                y[2 * (i * d + j)] = y[2 * (j * d + i)] = re;
-                y[2 * (i * d + j) + 1] = im;
-                y[2 * (j * d + i) + 1] = -im;
-                f += (i == j ? 1.0 : 2.0) * (re * re + im * im);
             }
+            for (int64_t j = 0; j < d; ++j) f += rr[j] * rr[j] + ri[j] * ri[j];
+        }
         f = std::sqrt(f);
         if (!(f > 0.0)) return (float)(n1 * (1.0 + 1e-6));
         lg = 2.0 * lg + std::log(f);
-        for (double& v : y) v /= f;
-        x.swap(y);
+        const double inv = 1.0 / f;
+        for (int64_t i = 0; i < d * d; ++i) {
+            xr[i] = yr[i] * inv;
+            xi[i] = yi[i] * inv;
+        }
     }
     return (float)(std::min(n1, n1 * std::exp(lg / (1 << squarings))) * (1.0 + 1e-6));
 }
@@ -764,12 +788,17 @@ pm_status prepare(pm_ctx* ctx, const pm::EngineInfo& e, bool keep_nodes, const d
     p.basis_lds = (e.kind == pm::ENGINE_MFMA && e.D == 16 &&
                    (size_t)ctx->M * e.D * e.D * 16 <= 64 * 1024) ? 1 : 0;
     // two slices per tile for Taylor propagations of dimension <= 8 (also
-    // the checkpointed forward pass: its chain products and tree nodes come
-    // out in the unpaired layout)
-    if (ctx->d_basis_pair && basis == ctx->d_basis && (ctx->method == PM_EXPM_TAYLOR || keep_nodes) &&
-        e.kind == pm::ENGINE_MFMA && e.D == 16 && (ctx->precision != PM_FP64 || ctx->M <= pm::kWaveBasis)) {
-        p.pair = 1;
-        p.basis = ctx->d_basis_pair;
+    // the checkpointed forward pass): FP64 on the 16-wide basis as it is while
+    // its weights fill a row of lanes, the reduced precisions on the basis in
+    // both diagonal blocks
+    const bool taylor = ctx->method == PM_EXPM_TAYLOR || keep_nodes;
+    if (e.kind == pm::ENGINE_MFMA && e.D == 16 && ctx->dim <= 8 && taylor && ctx->order != PM_ORDER_MAGNUS6) {
+        if (ctx->precision == PM_FP64) {
+            p.pair = ctx->M <= pm::kWaveBasis ? 1 : 0;
+        } else if (ctx->d_basis_pair) {
+            p.pair = 1;
+            p.basis = ctx->d_basis_pair;
+        }
     }
     std::memcpy(p.pair_a, ctx->pair_a, sizeof(p.pair_a));
     std::memcpy(p.pair_b, ctx->pair_b, sizeof(p.pair_b));
@@ -811,9 +840,6 @@ pm_status forward_keep(pm_ctx* ctx, const double* d_samples, int64_t n_samples, 
         const hipError_t he = pm::launch_propagate(e, PM_FP64, p, stream);
         if (he != hipSuccess) return hip_fail(ctx, he, "forward launch");
     }
-    // the backward and trajectory kernels recompute single slices
-    p.pair = 0;
-    p.basis = basis;
     return PM_OK;
 }
 
@@ -834,14 +860,15 @@ pm_status launch_grad(pm_ctx* ctx, const double* d_samples, int64_t n_samples, d
     gp.W = d_W;
     gp.UT = p.U_out;   // where the forward left U(T)
     gp.gw = ctx->d_gw;
-    // few long chains: split each into parts of at least four slices (each
-    // part recomputes its predecessors in the chain) until about 2048 waves
-    // run (D = 16: two waves per unit); shorter parts lose more to the
-    // recomputation than they gain
+    // few long chains: split each (pairs: each half) into parts of at least
+    // four slices until about a wave per SIMD runs; a part recomputes its
+    // predecessors in the chain, and shorter parts lose more to that than
+    // they gain
     gp.split = 1;
     gp.grad_direct = nullptr;
-    const int64_t max_units = e.D == 16 ? 1024 : 2048;
-    while (p.n_chains * gp.split * 2 <= max_units && p.chunk >= 8 * gp.split) gp.split *= 2;
+    const int64_t max_units = e.D <= 32 ? 1024 : 2048, run = p.pair ? (p.chunk + 1) / 2 : p.chunk;
+    while (p.n_chains * gp.split * 2 <= max_units && run >= 8 * gp.split) gp.split *= 2;
+    fill_adjoint(gp);
     he = pm::launch_backward(e.D, gp, d_grad, stream);
     if (he != hipSuccess) return hip_fail(ctx, he, "backward launch");
     return PM_OK;
@@ -1284,10 +1311,10 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
             if (he != hipSuccess) return hip_fail(ctx, he, "hipMemcpy gradient basis");
         }
     }
-    // slice pairs: the basis in both diagonal 8 x 8 blocks of the 16-wide
-    // tile, for dimensions <= 8 and at most 32 basis matrices
+    // slice pairs of the reduced precisions: the basis in both diagonal 8 x 8
+    // blocks of the 16-wide tile, for at most 32 basis matrices
     dfree(ctx->d_basis_pair);
-    if (e.kind == pm::ENGINE_MFMA && e.D == 16 && dim <= 8 && M <= 32 && order != PM_ORDER_MAGNUS6) {
+    if (e.kind == pm::ENGINE_MFMA && e.D == 16 && dim <= 8 && M <= 32 && ctx->precision != PM_FP64) {
         std::vector<double> dual((size_t)M * 16 * 16 * 2, 0.0);
         for (int m = 0; m < M; ++m)
             for (int64_t r = 0; r < dim; ++r)

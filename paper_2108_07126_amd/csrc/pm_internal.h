@@ -60,13 +60,16 @@ struct PropParams {
     int K, M, order, du;
     int max_degree, force_s;
     int basis_lds;               // MFMA engine: block keeps a copy of the basis in LDS
-    int pair;                    // MFMA engine, D = 16: two slices of dimension <= 8 per tile
+    int pair;                    // MFMA engines, D = 16: two slices of dimension <= 8 per tile
     int method;                  // PM_EXPM_TAYLOR or PM_EXPM_CHEBYSHEV
     const double* cheb_j;        // Chebyshev: [m][k] = J_k(ctheta[m]), k <= m <= kMaxCheb; then the split rows
     double ctheta[kMaxCheb + 1]; // Chebyshev: half-width of the spectral interval for degree m
     uint8_t pair_a[kMaxBasis];   // order 4: control indices of i[H_a, H_b]
     uint8_t pair_b[kMaxBasis];
 };
+
+// Terms of the adjoint's series at most (adjoint_kernel.h).
+constexpr int kAdjointTerms = 24;
 
 // The gradient kernels' arguments.
 struct GradParams {
@@ -75,8 +78,10 @@ struct GradParams {
     const double* UT;   // [du][du] complex128, U(T) of that forward
     double* gw;         // [N][M] dL / d w_{j,m}
     int split;          // backward units per chain (>= 1): unit u covers part u % split of chain u / split
-    double* grad_direct;  // order 2 on the pipelined backward: dL/d samples written there directly
+    double* grad_direct;  // order 2 on one-wave teams: dL/d samples written there directly
                           // (dL/dc_k(j) = h dL/dw_{j,1+k}), no separate chain-rule kernel; else null
+    double adth[kAdjointTerms];      // one-wave teams: largest ||K|| that n + 1 terms serve
+    double inv[kAdjointTerms + 2];   // 1 / k
 };
 
 // Trajectory kernel arguments (PM_TRAJ_* kinds of the public header).

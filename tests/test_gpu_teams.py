@@ -108,3 +108,85 @@ def test_ragged_trees(pm, d):
             U = ctx.equiprop(w.samples, w.h)
         Uo = orc.propagate(w.H0, w.Hk, w.samples, w.h, 2)
         assert orc.relative_frobenius(U, Uo) <= 64 * math.sqrt(w.n_slices * d) * 2.0 ** -53, chains
+
+
+def gradient_case(pm, w, V, chunk=0):
+    import torch
+    Uo = orc.propagate(w.H0, w.Hk, w.samples, w.h, w.order)
+    _, go = orc.control_gradient(w.H0, w.Hk, w.samples, w.h, w.order, V)
+    with pm.Context(0, pm.PM_FP64) as ctx:
+        ctx.set_hamiltonian(w.H0, w.Hk, w.order)
+        if chunk:
+            ctx.set_chunk(chunk)
+        s = torch.from_numpy(w.samples).cuda()
+        g, U = torch.zeros_like(s), torch.zeros((w.dim, w.dim), dtype=torch.complex128, device="cuda")
+        ctx.backward_dev(s, w.h, torch.from_numpy(V).cuda(), g, U)
+        torch.cuda.synchronize()
+        g, U = g.cpu().numpy(), U.cpu().numpy()
+    # the adjoint multiplies the checkpoint and its conjugate (two products a
+    # slice before it) and a series of products of the slice's exponent: the
+    # propagation's bound four times over, relative to the gradient's scale
+    n, d = w.n_slices, w.dim
+    tol = 4 * 64 * math.sqrt(n * d) * 2.0 ** -53
+    scale = w.h * np.linalg.norm(V) * max(np.linalg.norm(h, 2) for h in w.Hk)
+    err = float(np.max(np.abs(g - go))) / scale
+    print(f"  gradient error {err:.2e} (bound {tol:.2e})", file=sys.stderr, flush=True)
+    assert err <= tol
+    assert orc.relative_frobenius(U, Uo) <= tol
+
+
+def cotangent(d, tag):
+    rng = np.random.default_rng(tag)
+    return rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d))
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 5, 8, 9, 12, 13, 16, 17, 24, 25, 32, 33])
+def test_adjoint_dimensions(pm, d):
+    """The adjoint where its instances change, a single slice, an odd pair of
+    halves, ragged last chains and blocks, and orders 2, 4 and CF4."""
+    for n, order, chunk in ((1, 2, 0), (3, 4, 0), (37, 2, 5), (67, 4, 1), (30, orc.CF4, 6)):
+        w = synth.random_system(d, 2, n_slices=n, h=0.05, order=order, tag=900 + d)
+        print(f"[case] adjoint d={d} N={n} order={order} chunk={chunk}", file=sys.stderr, flush=True)
+        gradient_case(pm, w, cotangent(d, d), chunk)
+
+
+@pytest.mark.parametrize("d,K", [(4, 6), (8, 5), (16, 4), (16, 5), (32, 2), (32, 3), (32, 8)])
+def test_adjoint_basis_sizes(pm, d, K):
+    for order in (2, 4):
+        w = synth.random_system(d, K, n_slices=19, h=0.05, order=order, tag=930 + d)
+        gradient_case(pm, w, cotangent(d, K))
+
+
+@pytest.mark.parametrize("d", [3, 8, 16, 32])
+def test_adjoint_norms_and_splits(pm, d):
+    """From two terms to the doubled series (||G|| up to 12), and long chains
+    split into parts that recompute their predecessors."""
+    for norm in (1e-8, 1e-3, 0.3, 0.9, 2.5, 12.0):
+        w = synth.random_system(d, 2, n_slices=11, h=norm, order=2, tag=950)
+        print(f"[case] adjoint d={d} norm={norm}", file=sys.stderr, flush=True)
+        gradient_case(pm, w, cotangent(d, 7))
+    for n, chunk in ((200, 32), (515, 128), (64, 64)):
+        w = synth.random_system(d, 1, n_slices=n, h=0.04, order=2, tag=960)
+        gradient_case(pm, w, cotangent(d, 8), chunk)
+
+
+@pytest.mark.parametrize("d", [1, 3, 4, 5, 8, 9, 16, 24, 32])
+def test_trajectory_dimensions(pm, d):
+    """Prefixes, states and density matrices with odd halves and ragged chains."""
+    rng = np.random.default_rng(d)
+    for n, order, chunk in ((1, 2, 0), (2, 4, 0), (41, 2, 7), (33, orc.CF4, 6)):
+        w = synth.random_system(d, 2, n_slices=n, h=0.05, order=order, tag=970 + d)
+        P = orc.trajectory(w.H0, w.Hk, w.samples, w.h, order)
+        nv = min(3, d)
+        psi = rng.standard_normal((d, nv)) + 1j * rng.standard_normal((d, nv))
+        rho = rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d))
+        print(f"[case] trajectory d={d} N={n} order={order} chunk={chunk}", file=sys.stderr, flush=True)
+        with pm.Context(0, pm.PM_FP64) as ctx:
+            ctx.set_hamiltonian(w.H0, w.Hk, order)
+            if chunk:
+                ctx.set_chunk(chunk)
+            tol = 2 * 64 * math.sqrt(n * d) * 2.0 ** -53
+            for kind, x0, ref in ((pm.PM_TRAJ_PROPAGATORS, None, P), (pm.PM_TRAJ_STATES, psi, P @ psi),
+                                  (pm.PM_TRAJ_DENSITY, rho, P @ rho @ P.conj().transpose(0, 2, 1))):
+                out = ctx.trajectory(w.samples, w.h, kind, x0)
+                assert np.max(np.abs(out - ref)) <= tol * max(1.0, float(np.max(np.abs(ref)))) * math.sqrt(d), (kind, n)
