@@ -325,49 +325,44 @@ __device__ __forceinline__ Mat<D, T> exp_ch(Herm<D, T> x, int m, const double* j
     ch_coeffs<D>(pw, r);
     if constexpr (KIND == EXP_CHEBYSHEV) ch_clenshaw<D>(r, m, jk, cre, cim);
     else ch_taylor<D, KIND == EXP_TAYLOR_EXCESS>(r, m, cre, cim);
-    // U = sum_i c_i X^i; (X^i)_{ba} = conj((X^i)_{ab})
+    // U = A + i B with the Hermitian A = sum_i Re(c_i) X^i and
+    // B = sum_i Im(c_i) X^i: an entry pair shares their entries,
+    // U_ab = A_ab + i B_ab, U_ba = conj(A_ab) + i conj(B_ab): half the
+    // operations of sum_i c_i (X^i)_ab entry by entry, in kernels bound by
+    // vector issue (with every slice stored: one qubit, 2^22 slices,
+    // 110 -> 74 us; two qubits in FP32, 2^20 slices, 104 -> 87 us)
     Mat<D, T> U;
 #pragma unroll
     for (int a = 0; a < D; ++a)
 #pragma unroll
         for (int b = a; b < D; ++b) {
             const int e = hidx<D>(a, b);
-            double xr[D], xi[D];
-            xr[0] = (a == b) ? 1.0 : 0.0;
-            xi[0] = 0.0;
-            xr[1] = x.re[e];
-            xi[1] = x.im[e];
+            double ar = cre[1] * x.re[e], ai = cre[1] * x.im[e];
+            double br = cim[1] * x.re[e], bi = cim[1] * x.im[e];
+            if (a == b) {
+                ar += cre[0];
+                br += cim[0];
+            }
             if constexpr (D == 4) {
-                xr[2] = x2.re[e];
-                xi[2] = x2.im[e];
                 // (X^3)_{ab} = sum_k X_{ak} (X^2)_{kb}
                 double tr = 0.0, ti = 0.0;
 #pragma unroll
                 for (int k = 0; k < D; ++k) {
-                    const double ar = x.gre(a, k), ai = x.gim(a, k);
-                    const double br = x2.gre(k, b), bi = x2.gim(k, b);
-                    tr = fma(ar, br, fma(-ai, bi, tr));
-                    ti = fma(ar, bi, fma(ai, br, ti));
+                    const double xr = x.gre(a, k), xi = x.gim(a, k);
+                    const double yr = x2.gre(k, b), yi = x2.gim(k, b);
+                    tr = fma(xr, yr, fma(-xi, yi, tr));
+                    ti = fma(xr, yi, fma(xi, yr, ti));
                 }
-                xr[3] = tr;
-                xi[3] = ti;
+                ar = fma(cre[2], x2.re[e], fma(cre[3], tr, ar));
+                ai = fma(cre[2], x2.im[e], fma(cre[3], ti, ai));
+                br = fma(cim[2], x2.re[e], fma(cim[3], tr, br));
+                bi = fma(cim[2], x2.im[e], fma(cim[3], ti, bi));
             }
-            // sum_i c_i x_i and sum_i c_i conj(x_i)
-            double pr = 0.0, pi = 0.0, qr = 0.0, qi = 0.0;
-#pragma unroll
-            for (int i = 0; i < D; ++i) {
-                const double rr = cre[i] * xr[i], ii = cim[i] * xi[i];
-                const double ri = cre[i] * xi[i], ir = cim[i] * xr[i];
-                pr += rr - ii;
-                pi += ri + ir;
-                qr += rr + ii;
-                qi += ir - ri;
-            }
-            U.re[a * D + b] = (T)pr;
-            U.im[a * D + b] = (T)pi;
+            U.re[a * D + b] = (T)(ar - bi);
+            U.im[a * D + b] = (T)(ai + br);
             if (a != b) {
-                U.re[b * D + a] = (T)qr;
-                U.im[b * D + a] = (T)qi;
+                U.re[b * D + a] = (T)(ar + bi);
+                U.im[b * D + a] = (T)(br - ai);
             }
         }
     return U;
@@ -629,6 +624,10 @@ __device__ __forceinline__ void store_phased(const PropParams& p, int64_t j, con
 // segments cooperatively, 16 bytes per lane, whole lines per instruction.
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
+// Doubles valu_tree needs at the start of the block's LDS.
+template <int D>
+constexpr int valu_tree_doubles() { return 2 * D * D * (kFanIn + 4); }
+
 template <typename T, int D>
 struct Stage {
     static constexpr int SB = D * D * 2 * (int)sizeof(T);   // bytes per slice
@@ -715,6 +714,99 @@ __device__ __forceinline__ void dummy_flush(const PropParams& p, int lane) {
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
+}
+
+// The block's four consecutive chains combined in LDS (later chain on the
+// left; W in lane 0 of each wave), then the ticketed product tree with fan-in
+// kFanIn over the blocks' products (FP64).  The first wave carries the
+// block's node: its doubles go out one per lane as agent-scope atomic stores,
+// and the group's last arrival reads all its nodes at once, one double per
+// lane and pass, hands node q to lane q and multiplies them pairwise across
+// lanes: a level costs one round of stores, the ticket and one round of
+// loads, without the L2 writeback and invalidate of a fence pair
+// (node_store_coherent).  lds: valu_tree_doubles<D>().  10^4 slices of one
+// qubit, where the launch and this tail are most of the call: 19.1 -> 17.9 us.
+template <int D>
+__device__ void valu_tree(const PropParams& p, Mat<D, double> W, int lane, int wib, double* lds) {
+    constexpr int NN = 2 * D * D;
+    double* comb = lds;
+    double* nds = lds + 4 * NN;
+    auto put = [&](double* at, const Mat<D, double>& X) {
+#pragma unroll
+        for (int e = 0; e < D * D; ++e) {
+            at[2 * e + 0] = X.re[e];
+            at[2 * e + 1] = X.im[e];
+        }
+    };
+    auto get = [&](const double* at) {
+        Mat<D, double> O;
+#pragma unroll
+        for (int e = 0; e < D * D; ++e) {
+            O.re[e] = at[2 * e + 0];
+            O.im[e] = at[2 * e + 1];
+        }
+        return O;
+    };
+    __syncthreads();
+    if (lane == 0) put(comb + wib * NN, W);
+    __syncthreads();
+    if (wib != 0) return;
+    // lane q takes chain q (q < 4), then pairs
+    auto reduce = [&](Mat<D, double> X, int count) {
+#pragma unroll
+        for (int delta = 1; delta < kFanIn; delta <<= 1) {
+            const Mat<D, double> later = mat_shfl_down<D>(X, delta);
+            const Mat<D, double> prod = mat_mul(later, X);
+            if ((lane & (2 * delta - 1)) == 0 && lane + delta < count) X = prod;
+        }
+        return X;
+    };
+    W = reduce(get(comb + (lane & 3) * NN), 4);
+    int64_t idx = blockIdx.x, cnt = p.n_leaves, off = 0;
+    while (cnt > 1) {
+        const int64_t pcnt = (cnt + kFanIn - 1) / kFanIn, poff = off + cnt, grp = idx / kFanIn;
+        const int64_t first = grp * kFanIn;
+        const int members = (int)(min(cnt, first + kFanIn) - first);
+        if (members > 1) {
+            wave_lds_sync();
+            if (lane == 0) put(comb, W);
+            wave_lds_sync();
+            double* node = p.nodes + (off + idx) * NN;
+            if (lane < NN) __hip_atomic_store(node + lane, comb[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0);
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            unsigned v = 0;
+            if (lane == 0) v = atomicAdd(&p.counters[poff + grp], 1u);
+            const unsigned t = (unsigned)wave_uniform((int)v);
+            if (t != (unsigned)(members - 1)) return;
+            if (lane == 0) atomicExch(&p.counters[poff + grp], 0u);
+            double* group = p.nodes + (off + first) * NN;
+            double x[kFanIn * NN / 64];
+#pragma unroll
+            for (int q = 0; q < kFanIn * NN / 64; ++q)
+                if (q * 64 + lane < members * NN)
+                    x[q] = __hip_atomic_load(group + q * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int q = 0; q < kFanIn * NN / 64; ++q)
+                if (q * 64 + lane < members * NN) nds[q * 64 + lane] = x[q];
+            wave_lds_sync();
+            W = reduce(get(nds + min(lane, members - 1) * NN), members);
+        }
+        idx = grp;
+        off = poff;
+        cnt = pcnt;
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int r = 0; r < D; ++r)
+#pragma unroll
+            for (int c = 0; c < D; ++c)
+                if (r < p.du && c < p.du) {
+                    p.U_out[(r * p.du + c) * 2 + 0] = W.re[r * D + c];
+                    p.U_out[(r * p.du + c) * 2 + 1] = W.im[r * D + c];
+                }
+    }
 }
 
 // One slice per lane, all matrices in registers.  A leaf (one wave) covers
@@ -945,101 +1037,21 @@ propagate_valu(PropParams p) {
         const Mat<D, double> prod = mat_mul(later, W);
         if ((lane & (2 * delta - 1)) == 0) W = prod;
     }
-    // lane 0 holds the wave's product; make it uniform
-#pragma unroll
-    for (int e = 0; e < D * D; ++e) {
-        W.re[e] = wave_uniform(__shfl(W.re[e], 0));
-        W.im[e] = wave_uniform(__shfl(W.im[e], 0));
-    }
-    // the block's four consecutive chains, combined in LDS (later chain on
-    // the left): the block is one leaf of the tree
-    double* comb = reinterpret_cast<double*>(stage_lds);
-    __syncthreads();
-    if (lane == 0) {
-#pragma unroll
-        for (int e = 0; e < D * D; ++e) {
-            comb[(wib * D * D + e) * 2 + 0] = W.re[e];
-            comb[(wib * D * D + e) * 2 + 1] = W.im[e];
-        }
-    }
-    __syncthreads();
-    if (wib != 0) return;
-#pragma unroll
-    for (int w = 1; w < 4; ++w) {
-        Mat<D, double> O;
-#pragma unroll
-        for (int e = 0; e < D * D; ++e) {
-            O.re[e] = comb[(w * D * D + e) * 2 + 0];
-            O.im[e] = comb[(w * D * D + e) * 2 + 1];
-        }
-        W = mat_mul(O, W);
-    }
-    // ticketed product tree with fan-in kFanIn over the blocks' products
-    // (FP64): a block publishes its node with a release fence before the
-    // group's ticket; only the group's last arrival acquires, multiplies the
-    // group's nodes (later on the left) and goes on
-    const int64_t NN = (int64_t)D * D * 2;
-    auto load_node = [&](int64_t at) {
-        const double* nd = p.nodes + at * NN;
-        Mat<D, double> O;
-#pragma unroll
-        for (int e = 0; e < D * D; ++e) {
-            O.re[e] = nd[2 * e + 0];
-            O.im[e] = nd[2 * e + 1];
-        }
-        return O;
-    };
-    int64_t idx = blockIdx.x, cnt = p.n_leaves, off = 0;
-    while (cnt > 1) {
-        const int64_t pcnt = (cnt + kFanIn - 1) / kFanIn, poff = off + cnt, grp = idx / kFanIn;
-        const int64_t first = grp * kFanIn;
-        const int64_t members = min(cnt, first + kFanIn) - first;
-        if (members > 1) {
-            double* node = p.nodes + (off + idx) * NN;
-            if (lane == 0) {
-#pragma unroll
-                for (int e = 0; e < D * D; ++e) {
-                    node[2 * e + 0] = W.re[e];
-                    node[2 * e + 1] = W.im[e];
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            unsigned v = 0;
-            if (lane == 0) v = atomicAdd(&p.counters[poff + grp], 1u);
-            const unsigned t = (unsigned)wave_uniform((int)__shfl(v, 0));
-            if (t != (unsigned)(members - 1)) return;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            if (lane == 0) atomicExch(&p.counters[poff + grp], 0u);
-            const int64_t lastn = first + members - 1;
-            Mat<D, double> P = lastn == idx ? W : load_node(off + lastn);
-            for (int64_t k = lastn - 1; k >= first; --k) P = mat_mul(P, k == idx ? W : load_node(off + k));
-            W = P;
-        }
-        idx = grp;
-        off = poff;
-        cnt = pcnt;
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int r = 0; r < D; ++r)
-#pragma unroll
-            for (int c = 0; c < D; ++c)
-                if (r < p.du && c < p.du) {
-                    p.U_out[(r * p.du + c) * 2 + 0] = W.re[r * D + c];
-                    p.U_out[(r * p.du + c) * 2 + 1] = W.im[r * D + c];
-                }
-    }
+    // lane 0 holds the wave's product
+    valu_tree<D>(p, W, lane, wib, reinterpret_cast<double*>(stage_lds));
 }
 
 template <typename T, int D, int ORD, int KB, int OUT>
 hipError_t launch_valu_k(const PropParams& p, hipStream_t stream) {
     const int64_t blocks = p.n_leaves;   // a block of four chains is a leaf
-    const size_t lds = 4 * (size_t)Stage<T, D>::BUF + sizeof(double) * (size_t)p.M * D * D * 2;
+    constexpr size_t bufs = 4 * (size_t)Stage<T, D>::BUF;
+    static_assert(bufs >= sizeof(double) * valu_tree_doubles<D>(), "the tree reuses the staging buffers");
+    const void* fn = (const void*)propagate_valu<T, D, ORD, KB, OUT>;
+    const size_t lds = bufs + sizeof(double) * (size_t)p.M * D * D * 2;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)propagate_valu<T, D, ORD, KB, OUT>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)(4 * (size_t)Stage<T, D>::BUF + sizeof(double) * kMaxBasis * D * D * 2));
+        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)(bufs + sizeof(double) * kMaxBasis * D * D * 2));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
