@@ -424,19 +424,21 @@ __device__ __forceinline__ void strip_store_root(const PropParams& p, const Stri
 // The ticketed product tree (fan-in kFanIn, see mfma_tree.h) of strip teams:
 // a team stores its node, releases it and takes its group's ticket; the last
 // arrival multiplies the group's nodes, the earliest first, reading each left
-// factor's adjoint straight from memory (its own node included).
+// factor's adjoint straight from memory (its own node included).  Waves past
+// the strips (active false) only keep the barriers.
 template <int NT, int KS>
-__device__ void strip_tree(const PropParams& p, int64_t leaf, Strip<NT> Q, const SLane& L, Slots& sl, int* tick) {
+__device__ void strip_tree(const PropParams& p, int64_t leaf, Strip<NT> Q, const SLane& L, Slots& sl, int* tick,
+                           bool active = true) {
     constexpr int64_t NN = (int64_t)256 * NT * NT * 2;
     int64_t idx = leaf, cnt = p.n_leaves, off = 0;
     while (cnt > 1) {
         const int64_t pcnt = (cnt + kFanIn - 1) / kFanIn, poff = off + cnt, grp = idx / kFanIn;
         const int64_t first = grp * kFanIn;
         const int64_t members = min(cnt, first + kFanIn) - first;
-        if (members > 1 || p.store_nodes) strip_node_store<NT>(p.nodes + (off + idx) * NN, Q, L);
+        if (active && (members > 1 || p.store_nodes)) strip_node_store<NT>(p.nodes + (off + idx) * NN, Q, L);
         if (members > 1) {
             __syncthreads();   // every wave's part of the node is stored
-            if (L.c == 0 && L.lane == 0) {
+            if (active && L.c == 0 && L.lane == 0) {
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
                 const unsigned v = atomicAdd(&p.counters[poff + grp], 1u);
                 if (v == (unsigned)(members - 1)) {
@@ -449,16 +451,19 @@ __device__ void strip_tree(const PropParams& p, int64_t leaf, Strip<NT> Q, const
             const int t = wave_uniform(*tick);
             __syncthreads();
             if (t != (int)(members - 1)) return;
-            Q = strip_node_load<NT>(p.nodes + (off + first) * NN, L);
+            if (active) Q = strip_node_load<NT>(p.nodes + (off + first) * NN, L);
             for (int64_t k = first + 1; k < first + members; ++k) {
-                const Strip<NT> X = strip_node_load_adj<NT>(p.nodes + (off + k) * NN, L);
-                Q = strip_mul<NT, KS>(strip_put<NT>(sl, X, L), Q, L);
+                char* s = sl.next();
+                if (active) strip_stage<NT>(s, strip_node_load_adj<NT>(p.nodes + (off + k) * NN, L), L);
+                __syncthreads();
+                if (active) Q = strip_mul<NT, KS>(s, Q, L);
             }
         }
         idx = grp;
         off = poff;
         cnt = pcnt;
     }
+    if (!active) return;
     if (p.store_nodes) strip_node_store<NT>(p.nodes + off * NN, Q, L);
     strip_store_root<NT>(p, Q, L);
 }
