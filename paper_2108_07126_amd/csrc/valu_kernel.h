@@ -138,17 +138,6 @@ __device__ __forceinline__ Mat<D, T> mat_convert(const Mat<D, U>& a) {
     return c;
 }
 
-template <int D>
-__device__ __forceinline__ Mat<D, double> mat_shfl_down(const Mat<D, double>& a, int delta) {
-    Mat<D, double> c;
-#pragma unroll
-    for (int e = 0; e < D * D; ++e) {
-        c.re[e] = __shfl_down(a.re[e], delta);
-        c.im[e] = __shfl_down(a.im[e], delta);
-    }
-    return c;
-}
-
 // Characteristic-polynomial coefficients r_0..r_{D-1} of a Hermitian X
 // (X^D = sum_i r_i X^i, Cayley-Hamilton) from the power traces
 // p_k = tr X^k by Newton's identities.
@@ -624,9 +613,14 @@ __device__ __forceinline__ void store_phased(const PropParams& p, int64_t j, con
 // segments cooperatively, 16 bytes per lane, whole lines per instruction.
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
-// Doubles valu_tree needs at the start of the block's LDS.
+// A D x D complex matrix in the product tree's LDS: entries as they are in
+// memory, padded so that neighbouring lanes' matrices start in other banks.
 template <int D>
-constexpr int valu_tree_doubles() { return 2 * D * D * (kFanIn + 4); }
+constexpr int tree_stride() { return 2 * D * D + 2; }
+
+// Bytes of LDS the product tree of a block takes (64 matrices per wave).
+template <int D>
+constexpr size_t valu_tree_bytes() { return sizeof(double) * 4 * 64 * tree_stride<D>(); }
 
 template <typename T, int D>
 struct Stage {
@@ -638,6 +632,12 @@ struct Stage {
     static constexpr int BUF = 64 * STRIDE;                  // bytes per wave
     static constexpr int PIECES = SEG / 16;                  // 16-byte pieces per segment
 };
+
+// The staging buffers of a block's four waves; the product tree reuses them.
+template <typename T, int D>
+constexpr size_t valu_stage_bytes() {
+    return 4 * (size_t)Stage<T, D>::BUF > valu_tree_bytes<D>() ? 4 * (size_t)Stage<T, D>::BUF : valu_tree_bytes<D>();
+}
 
 // The phased slice e^{-i mu} (U or I + U) into this lane's staging row.
 // A wave whose slices all have mu = 0 (traceless Hamiltonians) skips the
@@ -716,63 +716,84 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// The block's four consecutive chains combined in LDS (later chain on the
-// left; W in lane 0 of each wave), then the ticketed product tree with fan-in
-// kFanIn over the blocks' products (FP64).  The first wave carries the
-// block's node: its doubles go out one per lane as agent-scope atomic stores,
-// and the group's last arrival reads all its nodes at once, one double per
-// lane and pass, hands node q to lane q and multiplies them pairwise across
-// lanes: a level costs one round of stores, the ticket and one round of
-// loads, without the L2 writeback and invalidate of a fence pair
-// (node_store_coherent).  lds: valu_tree_doubles<D>().  10^4 slices of one
-// qubit, where the launch and this tail are most of the call: 19.1 -> 17.9 us.
+// Product of the `count` <= 64 matrices m + i * stride (i rising with time: later
+// ones on the left), pairwise, by one wave; the result replaces the first.  The
+// lanes share a level's entries: the D^2 ceil(count / 2) entries of a level take
+// the wave D FMAs of complex numbers per 64 of them, where a product per lane
+// with its operands shuffled in takes D^3 however few lanes hold one.  10^4
+// slices of two qubits (one slice per lane, two tree levels) 31 -> 20 us, of one
+// qubit 9.7 -> 8.9 us.
 template <int D>
-__device__ void valu_tree(const PropParams& p, Mat<D, double> W, int lane, int wib, double* lds) {
-    constexpr int NN = 2 * D * D;
-    double* comb = lds;
-    double* nds = lds + 4 * NN;
-    auto put = [&](double* at, const Mat<D, double>& X) {
+__device__ void wave_tree(double* m, int stride, int count, int lane) {
+    constexpr int E = D * D, MAXE = 32 * E / 64;
+    double re[MAXE], im[MAXE];
+    while (count > 1) {
+        const int pairs = count / 2, half = (count + 1) / 2;
 #pragma unroll
-        for (int e = 0; e < D * D; ++e) {
-            at[2 * e + 0] = X.re[e];
-            at[2 * e + 1] = X.im[e];
-        }
-    };
-    auto get = [&](const double* at) {
-        Mat<D, double> O;
+        for (int q = 0; q < MAXE; ++q) {
+            const int at = q * 64 + lane, pr = at / E, i = at / D % D, j = at % D;
+            if (q * 64 >= half * E) break;
+            if (pr < pairs) {
+                const double* a = m + (2 * pr + 1) * stride + 2 * D * i;
+                const double* b = m + 2 * pr * stride + 2 * j;
+                re[q] = im[q] = 0.0;
 #pragma unroll
-        for (int e = 0; e < D * D; ++e) {
-            O.re[e] = at[2 * e + 0];
-            O.im[e] = at[2 * e + 1];
+                for (int k = 0; k < D; ++k) {
+                    const double ar = a[2 * k], ai = a[2 * k + 1], br = b[2 * D * k], bi = b[2 * D * k + 1];
+                    re[q] = fma(ar, br, re[q]);
+                    re[q] = fma(-ai, bi, re[q]);
+                    im[q] = fma(ar, bi, im[q]);
+                    im[q] = fma(ai, br, im[q]);
+                }
+            } else if (pr < half) {
+                re[q] = m[2 * pr * stride + 2 * (at % E)];
+                im[q] = m[2 * pr * stride + 2 * (at % E) + 1];
+            }
         }
-        return O;
-    };
-    __syncthreads();
-    if (lane == 0) put(comb + wib * NN, W);
+        wave_lds_sync();
+#pragma unroll
+        for (int q = 0; q < MAXE; ++q) {
+            const int at = q * 64 + lane, pr = at / E;
+            if (pr < half) {
+                m[pr * stride + 2 * (at % E)] = re[q];
+                m[pr * stride + 2 * (at % E) + 1] = im[q];
+            }
+        }
+        wave_lds_sync();
+        count = half;
+    }
+}
+
+// The product of the block's lanes (W each: four chains of 64 consecutive runs) in
+// LDS, then the ticketed product tree with fan-in kFanIn over the blocks'
+// products (FP64).  The first wave carries the block's node: its doubles go out
+// one per lane as agent-scope atomic stores, and the group's last arrival reads
+// all its nodes at once, one double per lane and pass: a level costs one round
+// of stores, the ticket and one round of loads, without the L2 writeback and
+// invalidate of a fence pair (node_store_coherent).  lds: valu_tree_bytes<D>().
+template <int D>
+__device__ void valu_tree(const PropParams& p, const Mat<D, double>& W, int lane, int wib, double* lds) {
+    constexpr int NN = 2 * D * D, ST = tree_stride<D>();
+    __syncthreads();   // the block is done with what the LDS held
+    double* mine = lds + wib * 64 * ST;
+#pragma unroll
+    for (int e = 0; e < D * D; ++e) {
+        mine[lane * ST + 2 * e + 0] = W.re[e];
+        mine[lane * ST + 2 * e + 1] = W.im[e];
+    }
+    wave_lds_sync();
+    wave_tree<D>(mine, ST, 64, lane);
     __syncthreads();
     if (wib != 0) return;
-    // lane q takes chain q (q < 4), then pairs
-    auto reduce = [&](Mat<D, double> X, int count) {
-#pragma unroll
-        for (int delta = 1; delta < kFanIn; delta <<= 1) {
-            const Mat<D, double> later = mat_shfl_down<D>(X, delta);
-            const Mat<D, double> prod = mat_mul(later, X);
-            if ((lane & (2 * delta - 1)) == 0 && lane + delta < count) X = prod;
-        }
-        return X;
-    };
-    W = reduce(get(comb + (lane & 3) * NN), 4);
+    wave_tree<D>(lds, 64 * ST, 4, lane);
     int64_t idx = blockIdx.x, cnt = p.n_leaves, off = 0;
     while (cnt > 1) {
         const int64_t pcnt = (cnt + kFanIn - 1) / kFanIn, poff = off + cnt, grp = idx / kFanIn;
         const int64_t first = grp * kFanIn;
         const int members = (int)(min(cnt, first + kFanIn) - first);
         if (members > 1) {
-            wave_lds_sync();
-            if (lane == 0) put(comb, W);
-            wave_lds_sync();
             double* node = p.nodes + (off + idx) * NN;
-            if (lane < NN) __hip_atomic_store(node + lane, comb[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane < NN) __hip_atomic_store(node + lane, lds[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
             __builtin_amdgcn_s_waitcnt(0);
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -787,25 +808,23 @@ __device__ void valu_tree(const PropParams& p, Mat<D, double> W, int lane, int w
             for (int q = 0; q < kFanIn * NN / 64; ++q)
                 if (q * 64 + lane < members * NN)
                     x[q] = __hip_atomic_load(group + q * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-            for (int q = 0; q < kFanIn * NN / 64; ++q)
-                if (q * 64 + lane < members * NN) nds[q * 64 + lane] = x[q];
             wave_lds_sync();
-            W = reduce(get(nds + min(lane, members - 1) * NN), members);
+#pragma unroll
+            for (int q = 0; q < kFanIn * NN / 64; ++q) {
+                const int at = q * 64 + lane;
+                if (at < members * NN) lds[at / NN * ST + at % NN] = x[q];
+            }
+            wave_lds_sync();
+            wave_tree<D>(lds, ST, members, lane);
         }
         idx = grp;
         off = poff;
         cnt = pcnt;
     }
-    if (lane == 0) {
-#pragma unroll
-        for (int r = 0; r < D; ++r)
-#pragma unroll
-            for (int c = 0; c < D; ++c)
-                if (r < p.du && c < p.du) {
-                    p.U_out[(r * p.du + c) * 2 + 0] = W.re[r * D + c];
-                    p.U_out[(r * p.du + c) * 2 + 1] = W.im[r * D + c];
-                }
+    const int r = lane / D, c = lane % D;
+    if (r < p.du && c < p.du) {
+        p.U_out[(r * p.du + c) * 2 + 0] = lds[2 * lane];
+        p.U_out[(r * p.du + c) * 2 + 1] = lds[2 * lane + 1];
     }
 }
 
@@ -826,13 +845,13 @@ propagate_valu(PropParams p) {
     const int64_t wave = (int64_t)blockIdx.x * 4 + wib;
     extern __shared__ char stage_lds[];
     using S = Stage<T, D>;
-    // the block's copy of the basis (after the four staging buffers)
-    double* lbasis = reinterpret_cast<double*>(stage_lds + 4 * S::BUF);
+    // the block's copy of the basis (after the four staging buffers and the tree's space)
+    double* lbasis = reinterpret_cast<double*>(stage_lds + valu_stage_bytes<T, D>());
     block_copy_to_lds(lbasis, p.basis, p.M * D * D * 2);
     __syncthreads();
     char* sbuf = stage_lds + wib * S::BUF;
     char* srow = sbuf + lane * S::STRIDE;
-    // a lane's run is a multiple of 16 slices (two sample blocks, 2 S::R)
+    // a lane's run is whole segments (S::R slices)
     const int64_t cfirst = chain_first(p, wave);
     const int64_t run = wave < p.n_chains ? (chain_first(p, wave + 1) - cfirst) / 64 : 0;
     const int64_t base = cfirst + (int64_t)lane * run;
@@ -944,7 +963,10 @@ propagate_valu(PropParams p) {
 #pragma unroll
                 for (int r = 0; r < SB; ++r) {
                     step(slice_of(b, r), base + i0 + r, r % S::R);
-                    if ((r + 1) % S::R == 0) flush(i0 + r + 1);
+                    if ((r + 1) % S::R == 0) {
+                        flush(i0 + r + 1);
+                        if (i0 + r + 1 >= run) return;   // a short chain's run ends inside the block
+                    }
                     // the slices' exponentials are independent: keep the
                     // scheduler from overlapping them (their registers
                     // would spill)
@@ -959,6 +981,7 @@ propagate_valu(PropParams p) {
             for (int64_t i0 = 0; i0 < run; i0 += 2 * SB) {
                 load_block<KB, SB>(p, base + i0 + SB, B);
                 block(A, i0);
+                if (i0 + SB >= run) break;
                 load_block<KB, SB>(p, base + i0 + 2 * SB, A);
                 block(B, i0 + SB);
             }
@@ -1003,6 +1026,7 @@ propagate_valu(PropParams p) {
             for (int64_t i0 = 0; i0 < run; i0 += 2 * S::R) {
                 load_group(B, i0 + S::R);
                 group(A, i0);
+                if (i0 + S::R >= run) break;   // (a run holds whole segments)
                 load_group(A, i0 + 2 * S::R);
                 group(B, i0 + S::R);
             }
@@ -1029,23 +1053,13 @@ propagate_valu(PropParams p) {
             Qx.im[e] = cs * im - sn * r;
         }
     }
-    // product over the wave's 64 consecutive runs: lane l+delta holds later slices
-    Mat<D, double> W = Qx;
-#pragma unroll
-    for (int delta = 1; delta < 64; delta <<= 1) {
-        const Mat<D, double> later = mat_shfl_down<D>(W, delta);
-        const Mat<D, double> prod = mat_mul(later, W);
-        if ((lane & (2 * delta - 1)) == 0) W = prod;
-    }
-    // lane 0 holds the wave's product
-    valu_tree<D>(p, W, lane, wib, reinterpret_cast<double*>(stage_lds));
+    valu_tree<D>(p, Qx, lane, wib, reinterpret_cast<double*>(stage_lds));
 }
 
 template <typename T, int D, int ORD, int KB, int OUT>
 hipError_t launch_valu_k(const PropParams& p, hipStream_t stream) {
     const int64_t blocks = p.n_leaves;   // a block of four chains is a leaf
-    constexpr size_t bufs = 4 * (size_t)Stage<T, D>::BUF;
-    static_assert(bufs >= sizeof(double) * valu_tree_doubles<D>(), "the tree reuses the staging buffers");
+    constexpr size_t bufs = valu_stage_bytes<T, D>();
     const void* fn = (const void*)propagate_valu<T, D, ORD, KB, OUT>;
     const size_t lds = bufs + sizeof(double) * (size_t)p.M * D * D * 2;
     static bool attr_set = false;
