@@ -515,6 +515,42 @@ int tune_class(int D) {
     }
 }
 
+// Slices that the chains of an engine come in whole multiples of.  FP64 VALU
+// chains need whole output segments per lane; up to a chain per resident wave
+// they may be that short.  (More, or the reduced precisions, whose rounding
+// depends on where a chain starts: chunk_unit.)
+int64_t chain_unit(const pm_ctx* ctx, const pm::EngineInfo& e, int64_t N, int64_t chunk) {
+    if (e.kind != pm::ENGINE_VALU || ctx->precision != PM_FP64) return e.chunk_unit;
+    const int64_t u = e.D == 2 ? 128 : 64;
+    const int64_t c = (chunk + u - 1) / u * u;
+    return (N + c - 1) / c <= (int64_t)e.resident_chains || chunk >= e.chunk_unit ? u : e.chunk_unit;
+}
+
+// Automatic chain length of the FP64 VALU engine: a lane's run takes about
+// `slice` us per slice and a level of the tree (fan-in 8, four chains to a leaf)
+// about `level` us, so short propagations take the run and depth that cost
+// least together, and long ones spread evenly over the target count.  Whole
+// units of 1024 left most of the device idle below 2^21 slices and up to half of
+// it just above a multiple (one qubit: 10^4 slices 17.5 -> 9.2 us, 10^6 slices 30 ->
+// 20.5 us; two qubits: 10^4 slices 51 -> 20 us).
+int64_t fine_chunk(const pm::EngineInfo& e, int64_t N, int64_t target) {
+    const int64_t u = e.D == 2 ? 128 : 64;
+    const double slice = e.D == 2 ? 0.65 : 3.0, level = e.D == 2 ? 1.5 : 2.0;
+    int64_t best = 0;
+    double best_cost = 0.0;
+    for (int64_t chains = 4, levels = 0;; chains *= 8, ++levels) {
+        const int64_t n = std::min(chains, target) * u;
+        const int64_t c = (N + n - 1) / n * u;
+        const double cost = slice * (double)(c / 64) + level * (double)levels;
+        if (best == 0 || cost < best_cost) {
+            best = c;
+            best_cost = cost;
+        }
+        if (chains >= target) break;
+    }
+    return best;
+}
+
 // Chain length: about one chain per resident wave team (or the tuned count),
 // in whole units.  The tuned counts are measured on propagations that return
 // U(T) only; with per-slice output the two-dimensional VALU kernel keeps one
@@ -527,6 +563,7 @@ int64_t auto_chunk(const pm::EngineInfo& e, int64_t N, int precision, bool per_s
     const bool tuned = !(per_slice && e.kind == pm::ENGINE_VALU && e.D == 2);
     if (tuned && tc >= 0 && precision >= 0 && precision < 4 && g_tune_chains[tc][precision] > 0)
         target = g_tune_chains[tc][precision];
+    if (e.kind == pm::ENGINE_VALU && precision == PM_FP64) return fine_chunk(e, N, target);
     int64_t c = (N + target - 1) / target;
     if (c < 1) c = 1;
     // Short MFMA chains: below four slices the product tree's extra leaves
@@ -547,7 +584,8 @@ int64_t effective_chunk(const pm_ctx* ctx, const pm::EngineInfo& e, int64_t N, b
     if (ctx->call_chunk > 0) return ctx->call_chunk;
     int64_t c = ctx->chunk_override > 0 ? ctx->chunk_override
                                         : auto_chunk(e, N, ctx->precision, per_slice);
-    c = ((c + e.chunk_unit - 1) / e.chunk_unit) * e.chunk_unit;
+    const int64_t u = chain_unit(ctx, e, N, c);
+    c = ((c + u - 1) / u) * u;
     if (e.kind == pm::ENGINE_VALU && c > (int64_t(1) << 20)) c = int64_t(1) << 20;
     // CF4: a chain starts at a slice boundary (an even exponential index)
     if (ctx->order == PM_ORDER_CF4 && (c & 1)) ++c;
