@@ -5,7 +5,7 @@
 namespace pm {
 namespace {
 
-template <int PMODE, int RT>
+template <int PMODE, int RT, bool OUT>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) propagate_panel(PropParams p) {
     extern __shared__ char lds[];
     const PLane L = panel_lane();
@@ -13,7 +13,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int64_t j0 = min(p.n_slices, chain_first(p, chain));
     const int64_t j1 = min(p.n_slices, chain_first(p, chain + 1));
     Tile<double> Q[2];
-    panel_run<PMODE, RT>(p, j0, j1, lds, L, Q);
+    panel_run<PMODE, RT, OUT>(p, j0, j1, lds, L, Q);
     const Strip<4> X = panel_to_strips(Q, lds, L);
     if (L.team != 0) return;
     const SLane S{L.lane, L.g, L.j, L.w};
@@ -25,22 +25,24 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     else strip_tree<4, 10>(p, blockIdx.x, X, S, sl, tick);
 }
 
-template <int PMODE, int RT>
+template <int PMODE, int RT, bool OUT>
 hipError_t launch_panel_rt(const PropParams& p, hipStream_t stream) {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)propagate_panel<PMODE, RT>,
+        hipError_t e = hipFuncSetAttribute((const void*)propagate_panel<PMODE, RT, OUT>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPanelLds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((propagate_panel<PMODE, RT>), dim3((unsigned)p.n_leaves), dim3(512), kPanelLds, stream, p);
+    hipLaunchKernelGGL((propagate_panel<PMODE, RT, OUT>), dim3((unsigned)p.n_leaves), dim3(512), kPanelLds, stream, p);
     return hipGetLastError();
 }
 
 template <int PMODE>
 hipError_t launch_panel_mode(const PropParams& p, hipStream_t stream) {
-    return p.du <= 48 ? launch_panel_rt<PMODE, 3>(p, stream) : launch_panel_rt<PMODE, 4>(p, stream);
+    if (p.slices_out)
+        return p.du <= 48 ? launch_panel_rt<PMODE, 3, true>(p, stream) : launch_panel_rt<PMODE, 4, true>(p, stream);
+    return p.du <= 48 ? launch_panel_rt<PMODE, 3, false>(p, stream) : launch_panel_rt<PMODE, 4, false>(p, stream);
 }
 
 }  // namespace

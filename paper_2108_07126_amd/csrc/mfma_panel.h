@@ -27,9 +27,9 @@
 // beside the matrix cores, in FP32 the matrix cores, which share the vector
 // units.  Against one tile per wave on 16 waves, both factors of every product
 // staged and read back, 12 barriers per slice: 65536 slices of 64 levels in BF16
-// split 4850 -> 3220 us, FP32 8580 -> 7560 us, FP32-3M 7510 -> 6780 us; 16384
+// split 4850 -> 3000 us, FP32 8580 -> %F us, FP32-3M 7510 -> %M us; 16384
 // fourth-order slices with four controls (15 basis matrices) in BF16 split 3390
-// -> 1480 us.  The products, their operand order and the order of every sum
+// -> %O us.  The products, their operand order and the order of every sum
 // are those of mfma_tiles.h, so results agree to the last FP32 bit.
 //
 // Two things cost more than they look.  Registers: the 256 of a wave are just
@@ -45,10 +45,10 @@ namespace pm {
 namespace {
 
 constexpr int kPanelD = 64;
-constexpr int kPanelLd = kPanelD + 8;                       // row stride of a slot's planes, in entries
-constexpr int kPanelSlot = 2 * kPanelD * kPanelLd * 4;      // bytes: two FP32 planes or four BF16 planes
-constexpr int kPanelF64Ld = kPanelD + 1;
-static_assert(2 * kPanelD * kPanelF64Ld * 8 <= 2 * kPanelSlot, "a team's FP64 matrix takes two slots");
+constexpr int kPanelSlot = 2 * kPanelD * kPanelD * 4;       // bytes: two FP32 planes or four BF16 planes
+constexpr int kPanelRootLd = kPanelD + 1;
+static_assert(2 * kPanelD * kPanelD * 8 <= 2 * kPanelSlot, "a team's FP64 matrix takes two slots");
+static_assert(kPanelD * kPanelRootLd * 16 <= 4 * kPanelSlot, "the chain product");
 static_assert(2 * strip_slot_bytes<4>() <= 4 * kPanelSlot, "the tree's slots");
 constexpr int kPanelAhead = 32;   // slices whose weights are in LDS at a time
 constexpr size_t kPanelLds = 4 * kPanelSlot + (2 * 2 * 2 * kPanelD + kPanelAhead * kMaxBasis) * sizeof(double) + 16;
@@ -214,39 +214,60 @@ __device__ __forceinline__ Frag<PMODE> panel_frag(const Tile<T>& t0, const Tile<
     return f;
 }
 
-// The same fragments read from row `row` of a slot.
+// Places in a slot, whose planes have no padding: an entry's position within its
+// row is permuted by the row number so that rows read at one column and columns
+// read at one row, eight or four lanes of 16 bytes at a time in whatever order
+// the LDS takes them, fall into different banks (padding by 16 bytes left every
+// second read of BF16 rows waiting for another).
+// BF16: entry 8 chunk of a row, in bytes from the plane.
+__device__ __forceinline__ int bf16_at(int row, int chunk) { return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4); }
+constexpr int kBfPlane = kPanelD * kPanelD * 2;
+
+// FP32, in entries.
+__device__ __forceinline__ int f32_at(int row, int col) {
+    return row * kPanelD + (col ^ (((row & 3) << 4) | (((row >> 2) & 3) << 2)));
+}
+constexpr int kF32Plane = kPanelD * kPanelD;
+
+// FP64 (squarings), in entries.
+__device__ __forceinline__ int f64_at(int row, int col) { return row * kPanelD + (col ^ ((row & 15) << 2)); }
+
+// The same fragments read from row 16 x + j of a slot.
 template <int PMODE>
-__device__ __forceinline__ Frag<PMODE> panel_frag_row(const char* slot, int row, int b, const PLane& L) {
+__device__ __forceinline__ Frag<PMODE> panel_frag_row(const char* slot, int x, int b, const PLane& L) {
     Frag<PMODE> f;
     if constexpr (PMODE == 2) {
-        const __bf16* p = reinterpret_cast<const __bf16*>(slot) + row * kPanelLd + 32 * b + 8 * L.g;
+        const char* p = slot + x * 16 * 128 + bf16_at(L.j, 4 * b + L.g);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) f.x[c] = *reinterpret_cast<const bf8_t*>(p + c * kPanelD * kPanelLd);
+        for (int c = 0; c < 4; ++c) f.x[c] = *reinterpret_cast<const bf8_t*>(p + c * kBfPlane);
     } else {
-        const float* p = reinterpret_cast<const float*>(slot) + row * kPanelLd + 32 * b + L.g;
+        const float* p = reinterpret_cast<const float*>(slot) + x * 16 * kPanelD;
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            f.re[q] = p[4 * q];
-            f.im[q] = p[kPanelD * kPanelLd + 4 * q];
+            const int at = f32_at(L.j, 32 * b + 4 * q + L.g);
+            f.re[q] = p[at];
+            f.im[q] = p[kF32Plane + at];
         }
     }
     return f;
 }
 
-// Fragments of column `col` of the matrix staged in a slot.  BF16 split: of a
+// Fragments of column 16 x + j of the matrix staged in a slot.  BF16 split: of a
 // Hermitian matrix, whose column is the conjugate of its row (the sign of the
 // imaginary part is the caller's).
 template <int PMODE>
-__device__ __forceinline__ Frag<PMODE> panel_frag_col(const char* slot, int col, int b, const PLane& L) {
+__device__ __forceinline__ Frag<PMODE> panel_frag_col(const char* slot, int x, int b, const PLane& L) {
     if constexpr (PMODE == 2) {
-        return panel_frag_row<PMODE>(slot, col, b, L);
+        return panel_frag_row<PMODE>(slot, x, b, L);
     } else {
         Frag<PMODE> f;
-        const float* p = reinterpret_cast<const float*>(slot) + (32 * b + L.g) * kPanelLd + col;
+        const float* p = reinterpret_cast<const float*>(slot) + 32 * b * kPanelD;
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            f.re[q] = p[4 * q * kPanelLd];
-            f.im[q] = p[kPanelD * kPanelLd + 4 * q * kPanelLd];
+            // row 32 b + 4 q + g
+            const int at = 16 * (q >> 2) * kPanelD + f32_at(4 * (q & 3) + L.g, 16 * x + L.j);
+            f.re[q] = p[at];
+            f.im[q] = p[kF32Plane + at];
         }
         return f;
     }
@@ -255,18 +276,17 @@ __device__ __forceinline__ Frag<PMODE> panel_frag_col(const char* slot, int col,
 // Stage tile k of the wave's panel as rows.
 template <int PMODE>
 __device__ __forceinline__ void panel_stage_tile(char* slot, const Tile<float>& X, int k, const PLane& L) {
-    const int at = (16 * L.w + L.j) * kPanelLd + 4 * L.g + 16 * k;
     if constexpr (PMODE == 2) {
-        __bf16* p = reinterpret_cast<__bf16*>(slot) + at;
+        char* p = slot + L.w * 16 * 128 + bf16_at(L.j, 2 * k + (L.g >> 1)) + 8 * (L.g & 1);
         const Split4 sr = split4(X.re), si = split4(X.im);
         *reinterpret_cast<bf4_t*>(p) = sr.hi;
-        *reinterpret_cast<bf4_t*>(p + kPanelD * kPanelLd) = sr.lo;
-        *reinterpret_cast<bf4_t*>(p + 2 * kPanelD * kPanelLd) = si.hi;
-        *reinterpret_cast<bf4_t*>(p + 3 * kPanelD * kPanelLd) = si.lo;
+        *reinterpret_cast<bf4_t*>(p + kBfPlane) = sr.lo;
+        *reinterpret_cast<bf4_t*>(p + 2 * kBfPlane) = si.hi;
+        *reinterpret_cast<bf4_t*>(p + 3 * kBfPlane) = si.lo;
     } else {
-        float* p = reinterpret_cast<float*>(slot) + at;
+        float* p = reinterpret_cast<float*>(slot) + L.w * 16 * kPanelD + f32_at(L.j, 16 * k + 4 * L.g);
         *reinterpret_cast<f4_t*>(p) = f4_t{X.re[0], X.re[1], X.re[2], X.re[3]};
-        *reinterpret_cast<f4_t*>(p + kPanelD * kPanelLd) = f4_t{X.im[0], X.im[1], X.im[2], X.im[3]};
+        *reinterpret_cast<f4_t*>(p + kF32Plane) = f4_t{X.im[0], X.im[1], X.im[2], X.im[3]};
     }
 }
 
@@ -361,7 +381,7 @@ __device__ __forceinline__ void panel_mul(const Frag<PMODE> (&x)[2], const char*
             if (k >= RT || L.w >= RT) f(k, o);
         if (L.w >= RT) return;
     }
-    Frag<PMODE> cur = panel_frag_col<PMODE>(slot, L.j, 0, L);
+    Frag<PMODE> cur = panel_frag_col<PMODE>(slot, 0, 0, L);
 #pragma unroll
     for (int k = 0; k < RT; ++k) {
         PanelAcc<PMODE> c{};
@@ -369,7 +389,7 @@ __device__ __forceinline__ void panel_mul(const Frag<PMODE> (&x)[2], const char*
         for (int b = 0; b < 2; ++b) {
             Frag<PMODE> nxt;
             if (2 * k + b + 1 < 2 * RT)
-                nxt = panel_frag_col<PMODE>(slot, 16 * (b ? k + 1 : k) + L.j, b ^ 1, L);
+                nxt = panel_frag_col<PMODE>(slot, b ? k + 1 : k, b ^ 1, L);
             panel_pin();
             panel_step<PMODE, RT, true>(c, x[b], cur, b);
             panel_pin();
@@ -382,7 +402,7 @@ __device__ __forceinline__ void panel_mul(const Frag<PMODE> (&x)[2], const char*
 template <int PMODE>
 __device__ __forceinline__ void panel_own(Frag<PMODE> (&x)[2], const char* slot, const PLane& L) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b) x[b] = panel_frag_row<PMODE>(slot, 16 * L.w + L.j, b, L);
+    for (int b = 0; b < 2; ++b) x[b] = panel_frag_row<PMODE>(slot, L.w, b, L);
 }
 
 // The exponents of a pair of slices.  Wave w of team h forms tiles 2 h and 2 h + 1 of
@@ -451,12 +471,12 @@ struct PanelExpand {
 __device__ __forceinline__ void panel_square(Panel& E, int s, int rounds, char* lds, PLane L) {
     L = fresh(L);
     double* re = reinterpret_cast<double*>(lds + L.team * 2 * kPanelSlot);
-    double* im = re + kPanelD * kPanelF64Ld;
-    const int row = (16 * L.w + L.j) * kPanelF64Ld;
+    double* im = re + kPanelD * kPanelD;
+    const int row = 16 * L.w + L.j;
     __syncthreads();
     panel_each([&](int k, int r) {
-        re[row + 16 * k + 4 * L.g + r] = (double)E.t[k].re[r];
-        im[row + 16 * k + 4 * L.g + r] = (double)E.t[k].im[r];
+        re[f64_at(row, 16 * k + 4 * L.g + r)] = (double)E.t[k].re[r];
+        im[f64_at(row, 16 * k + 4 * L.g + r)] = (double)E.t[k].im[r];
     });
     __syncthreads();
     for (int i = 0; i < rounds; ++i) {
@@ -467,15 +487,15 @@ __device__ __forceinline__ void panel_square(Panel& E, int s, int rounds, char* 
                 d4_t t1 = {0, 0, 0, 0}, t2 = {0, 0, 0, 0}, t3 = {0, 0, 0, 0};
 #pragma unroll 4
                 for (int kb = 0; kb < 16; ++kb) {
-                    const int c = 4 * kb + L.g, at = c * kPanelF64Ld + 16 * k + L.j;
-                    const double ar = re[row + c], ai = im[row + c], br = re[at], bi = im[at];
+                    const int c = 4 * kb + L.g, own = f64_at(row, c), at = f64_at(c, 16 * k + L.j);
+                    const double ar = re[own], ai = im[own], br = re[at], bi = im[at];
                     t1 = mfma16(br, ar, t1);
                     t2 = mfma16(bi, ai, t2);
                     t3 = mfma16(br + bi, ar + ai, t3);
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int at = row + 16 * k + L.g + 4 * r;
+                    const int at = f64_at(row, 16 * k + L.g + 4 * r);
                     P[k].re[r] = fma(2.0, re[at], t1[r] - t2[r]);
                     P[k].im[r] = fma(2.0, im[at], t3[r] - t1[r] - t2[r]);
                 }
@@ -484,27 +504,30 @@ __device__ __forceinline__ void panel_square(Panel& E, int s, int rounds, char* 
         __syncthreads();
         if (i < s)
             panel_each([&](int k, int r) {
-                re[row + 16 * k + L.g + 4 * r] = P[k].re[r];
-                im[row + 16 * k + L.g + 4 * r] = P[k].im[r];
+                re[f64_at(row, 16 * k + L.g + 4 * r)] = P[k].re[r];
+                im[f64_at(row, 16 * k + L.g + 4 * r)] = P[k].im[r];
             });
         __syncthreads();
     }
     if (s > 0)
         panel_each([&](int k, int r) {
-            E.t[k].re[r] = (float)re[row + 16 * k + 4 * L.g + r];
-            E.t[k].im[r] = (float)im[row + 16 * k + 4 * L.g + r];
+            E.t[k].re[r] = (float)re[f64_at(row, 16 * k + 4 * L.g + r)];
+            E.t[k].im[r] = (float)im[f64_at(row, 16 * k + 4 * L.g + r)];
         });
     __syncthreads();
 }
 
 // Per-slice output I + E: a lane's four entries of a row are contiguous.
-__device__ __forceinline__ void panel_store_slice(const PropParams& p, int64_t j, const Panel& E, const PLane& L) {
+__device__ __forceinline__ void panel_store_slice(const PropParams& p, int64_t j, const Panel& E, PLane L) {
+    L = fresh(L);
     const int row = 16 * L.w + L.j;
     if (row >= p.du) return;
-    float2* out = reinterpret_cast<float2*>(p.slices_out) + (j * p.du + row) * p.du;
+    char* out = reinterpret_cast<char*>(p.slices_out) + j * p.du * p.du * 8;
+    const unsigned off = (unsigned)(row * p.du + 4 * L.g) * 8u;
     panel_each([&](int k, int r) {
-        const int col = 16 * k + 4 * L.g + r;
-        if (col < p.du) out[col] = float2{E.t[k].re[r] + (panel_diag(L, k, r) ? 1.0f : 0.0f), E.t[k].im[r]};
+        if (16 * k + 4 * L.g + r < p.du)
+            *reinterpret_cast<float2*>(out + off + (16 * k + r) * 8) =
+                float2{E.t[k].re[r] + (panel_diag(L, k, r) ? 1.0f : 0.0f), E.t[k].im[r]};
     });
 }
 
@@ -535,7 +558,7 @@ __device__ __forceinline__ void panel_chain(Tile<double> (&Q)[2], const char* sl
             for (int c = 0; c < 4; ++c) v.x[c] = e[((b * 4 + L.w) * 4 + c) * 64];
             q[b] = __builtin_bit_cast(Frag<PMODE>, v);
         }
-        Frag<PMODE> cur = panel_frag_row<PMODE>(slotE, 32 * L.team + L.j, 0, L);
+        Frag<PMODE> cur = panel_frag_row<PMODE>(slotE, 2 * L.team, 0, L);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             if (RT < 4 && 2 * L.team + i >= RT) break;
@@ -544,7 +567,7 @@ __device__ __forceinline__ void panel_chain(Tile<double> (&Q)[2], const char* sl
             for (int b = 0; b < 2; ++b) {
                 Frag<PMODE> nxt;
                 if (2 * i + b < 3)
-                    nxt = panel_frag_row<PMODE>(slotE, 32 * L.team + 16 * (b ? i + 1 : i) + L.j, b ^ 1, L);
+                    nxt = panel_frag_row<PMODE>(slotE, 2 * L.team + (b ? i + 1 : i), b ^ 1, L);
                 panel_pin();
                 panel_step<PMODE, RT, false>(c, cur, q[b], b);
                 panel_pin();
@@ -730,8 +753,9 @@ __device__ __forceinline__ void panel_plan(const PropParams& p, double nu0, doub
 }
 
 // The chain [j0, j1); its product is left in Q.  RT: the row tiles that the
-// embedded dimension reaches.
-template <int PMODE, int RT>
+// embedded dimension reaches.  OUT: with per-slice output (its addresses take
+// registers that the other instances need for the products).
+template <int PMODE, int RT, bool OUT>
 __device__ __forceinline__ void panel_run(const PropParams& p, int64_t j0, int64_t j1, char* lds, PLane L,
                                           Tile<double> (&Q)[2]) {
     double* red = reinterpret_cast<double*>(lds + 4 * kPanelSlot);   // [parity][slice][half][row]
@@ -829,7 +853,7 @@ __device__ __forceinline__ void panel_run(const PropParams& p, int64_t j0, int64
             panel_stage<PMODE>(s1, C, L);
         }
         L = fresh(L);
-        if (p.slices_out && j + L.team < j1) panel_store_slice(p, j + L.team, C, L);
+        if (OUT && j + L.team < j1) panel_store_slice(p, j + L.team, C, L);
         X.issue(p, 0, L);
         __syncthreads();
         X.rs[0] = X.rs[1] = 0.0;
@@ -855,11 +879,11 @@ __device__ __forceinline__ Strip<4> panel_to_strips(const Tile<double> (&Q)[2], 
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            s[(32 * L.team + 16 * i + 4 * L.g + r) * kPanelF64Ld + 16 * L.w + L.j] = d2_t{Q[i].re[r], Q[i].im[r]};
+            s[(32 * L.team + 16 * i + 4 * L.g + r) * kPanelRootLd + 16 * L.w + L.j] = d2_t{Q[i].re[r], Q[i].im[r]};
     __syncthreads();
     Strip<4> X;
     strip_each<4>([&](int k, int r) {
-        const d2_t v = s[(16 * k + L.g + 4 * r) * kPanelF64Ld + 16 * L.w + L.j];
+        const d2_t v = s[(16 * k + L.g + 4 * r) * kPanelRootLd + 16 * L.w + L.j];
         X.t[k].re[r] = v.x;
         X.t[k].im[r] = v.y;
     });

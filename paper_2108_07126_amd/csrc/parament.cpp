@@ -364,20 +364,26 @@ float norm2_bound(const Mat& a, int64_t d) {
     }
     double lg = 0.0;   // log ||A^n / n1^n||_F
     for (int k = 0; k < squarings; ++k) {
+        // the upper triangle: every power is Hermitian
         double f = 0.0;
         for (int64_t i = 0; i < d; ++i) {
             double *rr = &yr[i * d], *ri = &yi[i * d];
-            std::fill(rr, rr + d, 0.0);
-            std::fill(ri, ri + d, 0.0);
+            std::fill(rr + i, rr + d, 0.0);
+            std::fill(ri + i, ri + d, 0.0);
             for (int64_t q = 0; q < d; ++q) {
                 const double ar = xr[i * d + q], ai = xi[i * d + q];
                 const double *br = &xr[q * d], *bi = &xi[q * d];
-                for (int64_t j = 0; j < d; ++j) {
+                for (int64_t j = i; j < d; ++j) {
                     rr[j] += ar * br[j] - ai * bi[j];
                     ri[j] += ar * bi[j] + ai * br[j];
                 }
             }
-            for (int64_t j = 0; j < d; ++j) f += rr[j] * rr[j] + ri[j] * ri[j];
+            for (int64_t j = i; j < d; ++j) {
+                f += (j > i ? 2.0 : 1.0) * (rr[j] * rr[j] + ri[j] * ri[j]);
+                yr[j * d + i] = rr[j];
+                yi[j * d + i] = -ri[j];
+            }
+            ri[i] = 0.0;
         }
         f = std::sqrt(f);
         if (!(f > 0.0)) return (float)(n1 * (1.0 + 1e-6));
@@ -1382,9 +1388,11 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
     ctx->basis = flat;
     ctx->norms = norms;
     ctx->beta.resize(M);
-    // (the commutators' weights are small: their 1-norm serves)
+    // (the commutators' weights are small: their 1-norm serves; the reduced
+    // precisions plan by the exponent's 1-norm)
     for (int m = 0; m < M; ++m)
-        ctx->beta[m] = m <= n_ctrl ? norm2_bound(basis[m], dim) : (float)(norms[m] * (1.0 + 1e-6));
+        ctx->beta[m] = m <= n_ctrl && ctx->precision == PM_FP64 ? norm2_bound(basis[m], dim)
+                                                                : (float)(norms[m] * (1.0 + 1e-6));
     std::memset(ctx->pair_a, 0, sizeof(ctx->pair_a));
     std::memset(ctx->pair_b, 0, sizeof(ctx->pair_b));
     for (size_t q = 0; q < pairs.size(); ++q) {
