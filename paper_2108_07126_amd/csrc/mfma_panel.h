@@ -27,9 +27,9 @@
 // beside the matrix cores, in FP32 the matrix cores, which share the vector
 // units.  Against one tile per wave on 16 waves, both factors of every product
 // staged and read back, 12 barriers per slice: 65536 slices of 64 levels in BF16
-// split 4850 -> 3000 us, FP32 8580 -> %F us, FP32-3M 7510 -> %M us; 16384
+// split 4850 -> 3000 us, FP32 8580 -> 7400 us, FP32-3M 7510 -> 6570 us; 16384
 // fourth-order slices with four controls (15 basis matrices) in BF16 split 3390
-// -> %O us.  The products, their operand order and the order of every sum
+// -> 1310 us.  The products, their operand order and the order of every sum
 // are those of mfma_tiles.h, so results agree to the last FP32 bit.
 //
 // Two things cost more than they look.  Registers: the 256 of a wave are just
