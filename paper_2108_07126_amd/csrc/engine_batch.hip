@@ -3,7 +3,7 @@
 // One block of 16 waves per CU pulls packets from a shared counter until the
 // queue is empty (every block reaches its exit).  A packet holds up to
 // teams(D) consecutive chains of one instance (D = 16: 16 one-wave teams;
-// D = 32: 4 teams of 4 waves; D = 64: one team of 16 waves; dimensions below
+// D = 32: 4 teams of 4 waves; D = 64, in FP64: one team of 16 waves; dimensions below
 // 16 are embedded in 16).  The teams step through their chains in lockstep:
 // each step expands every team's slice, takes the largest ||G||_1 over the
 // teams for one shared (degree, squarings) plan, exponentiates and multiplies
@@ -11,8 +11,14 @@
 // whose exponential is exactly I.  The team products are then multiplied in
 // LDS (later chains on the left) and the packet's product enters its
 // instance's ticketed FP64 tree, whose root writes that instance's U(T).
+// In the reduced precisions the 64-wide packets, by far the largest, run on
+// panel teams (mfma_panel.h) in a kernel of blocks of eight waves beside this
+// one: either kernel's blocks fill a CU, and the smaller packets take over CUs
+// as the panel packets run out.  96 uneven systems of up to 64 levels in FP32-3M:
+// 8360 -> 7580 us.
 // Per-instance parameters live in device memory as PropParams records, so the
 // single-propagation helpers (weights, norms, planner, Taylor) serve as is.
+#include "mfma_panel.h"
 #include "mfma_tree.h"
 
 namespace pm {
@@ -131,18 +137,48 @@ __global__ void __launch_bounds__(1024) batch_kernel(BatchParams bp) {
     __shared__ int pk_sh;
     for (;;) {
         __syncthreads();
-        if (threadIdx.x == 0) pk_sh = (int)atomicAdd(bp.queue, 1u);
+        if (threadIdx.x == 0) pk_sh = bp.n_panel + (int)atomicAdd(bp.queue, 1u);
         __syncthreads();
         const int pk = pk_sh;
         if (pk >= bp.n_packets) break;
         const BatchPacket P = bp.packets[pk];
         if (P.D == 16) run_packet<T, PMODE, 16>(bp, P, dsm);
         else if (P.D == 32) run_packet<T, PMODE, 32>(bp, P, dsm);
-        else run_packet<T, PMODE, 64>(bp, P, dsm);
+        else if constexpr (std::is_same<T, double>::value) run_packet<T, PMODE, 64>(bp, P, dsm);
     }
 }
 
-__global__ void batch_reset(unsigned* queue) { *queue = 0u; }
+// One chain of a 64-wide instance, its product into the instance's tree.
+template <int PMODE, int RT>
+__device__ void run_panel_packet(const PropParams& p, const BatchPacket& P, char* lds, const PLane& L) {
+    const int64_t j0 = P.chain0 * p.chunk, j1 = min(p.n_slices, j0 + p.chunk);
+    Tile<double> Q[2];
+    panel_run<PMODE, RT, false>(p, j0, j1, lds, L, Q);
+    const Strip<4> X = panel_to_strips(Q, lds, L);
+    const SLane S{L.lane, L.g, L.j, L.w};
+    Slots sl{{lds, lds + strip_slot_bytes<4>()}, 0};
+    strip_tree<4, 4 * RT>(p, P.leaf, X, S, sl, reinterpret_cast<int*>(lds + kPanelLds - 16), L.team == 0);
+}
+
+template <int PMODE>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) batch_panel_kernel(BatchParams bp) {
+    extern __shared__ char lds[];
+    int* pk_sh = reinterpret_cast<int*>(lds + kPanelLds - 8);
+    const PLane L = panel_lane();
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) *pk_sh = (int)atomicAdd(bp.queue + 1, 1u);
+        __syncthreads();
+        const int pk = wave_uniform(*pk_sh);
+        if (pk >= bp.n_panel) break;
+        const BatchPacket P = bp.packets[pk];
+        const PropParams& p = bp.inst[P.inst];
+        if (p.du <= 48) run_panel_packet<PMODE, 3>(p, P, lds, L);
+        else run_panel_packet<PMODE, 4>(p, P, lds, L);
+    }
+}
+
+__global__ void batch_reset(unsigned* queue) { queue[0] = queue[1] = 0u; }
 
 template <int D>
 constexpr size_t batch_lds_for() {
@@ -155,13 +191,36 @@ constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
 constexpr size_t kBatchLds = cmax(batch_lds_for<16>(), cmax(batch_lds_for<32>(), batch_lds_for<64>()));
 
 template <typename T, int PMODE>
-hipError_t launch_batch_t(const BatchParams& bp, int blocks, hipStream_t stream) {
+hipError_t launch_batch_t(const BatchParams& bp, int blocks, hipStream_t stream, hipStream_t side, hipEvent_t fork,
+                          hipEvent_t join) {
+    const bool small = bp.n_packets > bp.n_panel;
+    if constexpr (!std::is_same<T, double>::value) {
+        if (bp.n_panel > 0) {
+            hipError_t e = hipSuccess;
+            if (small) e = hipEventRecord(fork, stream);
+            hipLaunchKernelGGL((batch_panel_kernel<PMODE>), dim3(blocks), dim3(512), kPanelLds, stream, bp);
+            if (e == hipSuccess) e = hipGetLastError();
+            if (!small || e != hipSuccess) return e;
+            e = hipStreamWaitEvent(side, fork, 0);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((batch_kernel<T, PMODE>), dim3(blocks), dim3(1024), kBatchLds, side, bp);
+            e = hipGetLastError();
+            if (e == hipSuccess) e = hipEventRecord(join, side);
+            if (e == hipSuccess) e = hipStreamWaitEvent(stream, join, 0);
+            return e;
+        }
+    }
     hipLaunchKernelGGL((batch_kernel<T, PMODE>), dim3(blocks), dim3(1024), kBatchLds, stream, bp);
     return hipGetLastError();
 }
 
 template <typename T, int PMODE>
 hipError_t allow_lds() {
+    if constexpr (!std::is_same<T, double>::value) {
+        const hipError_t e = hipFuncSetAttribute((const void*)batch_panel_kernel<PMODE>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPanelLds);
+        if (e != hipSuccess) return e;
+    }
     return hipFuncSetAttribute((const void*)batch_kernel<T, PMODE>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBatchLds);
 }
@@ -179,16 +238,18 @@ hipError_t batch_setup(int precision) {
     }
 }
 
-// Reset the queue and launch the persistent kernel (both capturable).
-hipError_t launch_batch(int precision, const BatchParams& bp, int blocks, hipStream_t stream) {
+// Reset the queues and launch the persistent kernels, the smaller packets' on
+// `side` between the two events if there are panel packets (all capturable).
+hipError_t launch_batch(int precision, const BatchParams& bp, int blocks, hipStream_t stream, hipStream_t side,
+                        hipEvent_t fork, hipEvent_t join) {
     hipLaunchKernelGGL(batch_reset, dim3(1), dim3(1), 0, stream, bp.queue);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     switch (precision) {
-        case PM_FP64: return launch_batch_t<double, 0>(bp, blocks, stream);
-        case PM_FP32: return launch_batch_t<float, 0>(bp, blocks, stream);
-        case PM_FP32_3M: return launch_batch_t<float, 1>(bp, blocks, stream);
-        case PM_BF16_SPLIT: return launch_batch_t<float, 2>(bp, blocks, stream);
+        case PM_FP64: return launch_batch_t<double, 0>(bp, blocks, stream, side, fork, join);
+        case PM_FP32: return launch_batch_t<float, 0>(bp, blocks, stream, side, fork, join);
+        case PM_FP32_3M: return launch_batch_t<float, 1>(bp, blocks, stream, side, fork, join);
+        case PM_BF16_SPLIT: return launch_batch_t<float, 2>(bp, blocks, stream, side, fork, join);
         default: return hipErrorInvalidValue;
     }
 }

@@ -19,7 +19,8 @@ namespace pm {
 hipError_t launch_mfma(int D, int precision, const PropParams& p, hipStream_t stream);
 hipError_t launch_valu(int D, bool fp64, const PropParams& p, hipStream_t stream);
 hipError_t launch_backward(int D, const GradParams& gp, double* grad_samples, hipStream_t stream);
-hipError_t launch_batch(int precision, const BatchParams& bp, int blocks, hipStream_t stream);
+hipError_t launch_batch(int precision, const BatchParams& bp, int blocks, hipStream_t stream, hipStream_t side,
+                        hipEvent_t fork, hipEvent_t join);
 hipError_t batch_setup(int precision);
 }  // namespace pm
 
@@ -1704,7 +1705,9 @@ struct pm_batch {
     pm::PropParams* d_inst = nullptr;
     pm::BatchPacket* d_packets = nullptr;
     unsigned* d_queue = nullptr;
-    hipStream_t cap = nullptr;
+    hipStream_t cap = nullptr, side = nullptr;   // graph capture
+    hipEvent_t fork = nullptr, join = nullptr;
+    int n_panel = 0;                             // leading packets that run on panel teams
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     int blocks = 0;
@@ -1727,6 +1730,13 @@ pm_status bhip(pm_batch* b, hipError_t e, const char* where) {
     b->broken = true;
     b->err = std::string(where) + ": " + hipGetErrorString(e);
     return PM_E_DEVICE;
+}
+
+void batch_streams_free(pm_batch* b) {
+    if (b->cap) (void)hipStreamDestroy(b->cap);
+    if (b->side) (void)hipStreamDestroy(b->side);
+    if (b->fork) (void)hipEventDestroy(b->fork);
+    if (b->join) (void)hipEventDestroy(b->join);
 }
 
 void batch_free(pm_batch* b) {
@@ -1785,10 +1795,14 @@ pm_status pm_batch_create(pm_batch** out, int device, int precision) {
         delete b;
         return create_fail(PM_E_DEVICE, "batch kernel setup (dynamic LDS attribute)", se);
     }
-    const hipError_t ce = hipStreamCreate(&b->cap);
+    hipError_t ce = hipStreamCreate(&b->cap);
+    if (ce == hipSuccess) ce = hipStreamCreate(&b->side);
+    if (ce == hipSuccess) ce = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
+    if (ce == hipSuccess) ce = hipEventCreateWithFlags(&b->join, hipEventDisableTiming);
     if (ce != hipSuccess) {
+        batch_streams_free(b);
         delete b;
-        return create_fail(PM_E_DEVICE, "capture stream", ce);
+        return create_fail(PM_E_DEVICE, "capture streams", ce);
     }
     *out = b;
     return PM_OK;
@@ -1800,7 +1814,7 @@ pm_status pm_batch_destroy(pm_batch* b) {
         DeviceGuard g(b->device);
         (void)hipDeviceSynchronize();
         batch_free(b);
-        if (b->cap) (void)hipStreamDestroy(b->cap);
+        batch_streams_free(b);
     }
     delete b;
     return PM_OK;
@@ -1910,6 +1924,10 @@ pm_status pm_batch_set(pm_batch* b, const pm_instance* inst, int64_t n_inst) {
     };
     std::stable_sort(packets.begin(), packets.end(),
                      [&](const pm::BatchPacket& a, const pm::BatchPacket& c) { return cost(a) > cost(c); });
+    const auto small = std::stable_partition(packets.begin(), packets.end(), [&](const pm::BatchPacket& x) {
+        return x.D == 64 && b->precision != PM_FP64;
+    });
+    const int n_panel = (int)(small - packets.begin());
 
     DeviceGuard g(b->device);
     if (!g.ok) return bhip(b, hipErrorInvalidDevice, "hipSetDevice");
@@ -1922,7 +1940,7 @@ pm_status pm_batch_set(pm_batch* b, const pm_instance* inst, int64_t n_inst) {
     if (he == hipSuccess) he = upload(&b->d_counters, nullptr, (size_t)counters_n * sizeof(unsigned));
     if (he == hipSuccess) he = hipMemset(b->d_counters, 0, std::max<size_t>((size_t)counters_n * sizeof(unsigned), 256));
     if (he == hipSuccess) he = upload(&b->d_out, nullptr, (size_t)out_d * sizeof(double));
-    if (he == hipSuccess) he = upload(&b->d_queue, nullptr, sizeof(unsigned));
+    if (he == hipSuccess) he = upload(&b->d_queue, nullptr, 2 * sizeof(unsigned));
     if (he != hipSuccess) {
         (void)hipGetLastError();
         batch_free(b);
@@ -1946,6 +1964,7 @@ pm_status pm_batch_set(pm_batch* b, const pm_instance* inst, int64_t n_inst) {
     }
     b->inst = P;
     b->packets = packets;
+    b->n_panel = n_panel;
     b->out_doubles = out_d;
     b->err.clear();
     return PM_OK;
@@ -1963,10 +1982,11 @@ pm_status pm_batch_run(pm_batch* b, void* stream) {
         bp.inst = b->d_inst;
         bp.packets = b->d_packets;
         bp.n_packets = (int)b->packets.size();
+        bp.n_panel = b->n_panel;
         bp.queue = b->d_queue;
         he = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
         if (he != hipSuccess) return bhip(b, he, "hipStreamBeginCapture");
-        he = pm::launch_batch(b->precision, bp, b->blocks, b->cap);
+        he = pm::launch_batch(b->precision, bp, b->blocks, b->cap, b->side, b->fork, b->join);
         hipGraph_t gr = nullptr;
         const hipError_t he2 = hipStreamEndCapture(b->cap, &gr);
         if (he != hipSuccess) return bhip(b, he, "batch launch");

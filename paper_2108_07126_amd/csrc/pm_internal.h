@@ -124,7 +124,8 @@ struct BatchParams {
     const PropParams* inst;      // device array, one record per instance
     const BatchPacket* packets;  // in execution order
     int n_packets;
-    unsigned* queue;             // next packet; zeroed before every launch
+    int n_panel;                 // the first n_panel packets run on panel teams
+    unsigned* queue;             // next packet, next panel packet; zeroed before every launch
 };
 
 constexpr int batch_teams(int D) { return D == 16 ? 16 : (D == 32 ? 4 : 1); }
