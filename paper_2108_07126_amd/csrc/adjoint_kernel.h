@@ -255,8 +255,6 @@ __attribute__((amdgpu_waves_per_eu(S::NT == 1 ? 2 : 1, S::NT == 1 ? 8 : 1))) adj
         // lanes through LDS, four matrices at a time (row q of lanes sums
         // matrix m0 + q, four lanes' values each)
         constexpr int R = S::kPair ? S::KS : 4;
-        const int64_t j = sl.second ? cm + t : c0 + t;   // this lane's slice; its row's below
-        (void)j;
         const int row = L.lane >> 4, l16 = L.lane & 15;
         const int64_t js = S::kPair && l16 >= 8 ? cm + t : c0 + t;
         const bool write = (l16 & (S::kPair ? 7 : 15)) == 0 && js < (S::kPair && l16 >= 8 ? c1 : cm);

@@ -123,40 +123,7 @@ __device__ __forceinline__ int min_squarings(double nu, double th) {
 // m <= max_degree; ties go to the smaller s.  Degrees 1, 2 and odd m >= 3
 // are the only candidates (an even m >= 4 costs as much as m + 1).  With
 // force_s >= 0 the smallest feasible degree is taken (max_degree if none).
-// Unrolled over the candidates so the thresholds stay in scalar registers.
-__device__ __forceinline__ void plan_expm(const PropParams& p, double nu, int& m_out, int& s_out) {
-    constexpr int kCand[12] = {1, 2, 3, 5, 7, 9, 11, 13, 15, 17, 19, 21};
-    const int md = p.max_degree;
-    int bm = md, bs = 0, bc = 1 << 30;
-    if (p.force_s >= 0) {
-        const double x = ldexp(nu, -p.force_s);
-#pragma unroll
-        for (int i = 11; i >= 0; --i) {
-            const int c = kCand[i];
-            if (c <= md && p.theta[c] >= x) bm = c;
-        }
-        m_out = bm;
-        s_out = p.force_s;
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < 12; ++i) {
-        const int c = kCand[i];
-        if (c <= md) {
-            const int s = min_squarings(nu, p.theta[c]);
-            const int cost = taylor_products(c) + s;
-            if (cost < bc || (cost == bc && s < bs)) {
-                bc = cost;
-                bm = c;
-                bs = s;
-            }
-        }
-    }
-    m_out = bm;
-    s_out = bs;
-}
-
-// The same plan with the 12 candidate degrees spread over lanes 0..11 (one
+// The 12 candidate degrees are spread over lanes 0..11 (one
 // candidate each, threshold preloaded in `lane_theta`, +inf elsewhere):
 // every lane packs (cost, s, candidate) into an integer key, and the row
 // minimum of the keys is the plan (ties to the smaller s, as above).
