@@ -577,8 +577,11 @@ int64_t auto_chunk(const pm::EngineInfo& e, int64_t N, int precision, bool per_s
     // cost more than the parallelism gains.  Measured on the d=16 workload
     // (graph replay): N = 8192, chains of 4 (512 blocks, uneven chains) 52.7
     // us, of 8 53.9 us, of 2 75.1 us; N = 4096 gradient, chains of 4 beat 2
-    // by 13 % and 8 by 30 %.
-    const int64_t cmin = 4;
+    // by 13 % and 8 by 30 %.  Above 16 levels in FP64 a slice takes one wave (one
+    // CU above 32) 10 us and more, a level of the tree as much: there a chain
+    // per SIMD (CU) comes first (27 levels: 1000 slices of a gradient 348 -> 187 us,
+    // 3000 fourth-order slices 142 -> 121 us; 64 levels, 600 slices 284 -> 244 us).
+    const int64_t cmin = precision == PM_FP64 && e.D > 16 ? 1 : 4;
     if (e.kind == pm::ENGINE_MFMA && c < cmin) c = cmin;
     const int64_t u = e.chunk_unit;
     return ((c + u - 1) / u) * u;
