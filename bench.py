@@ -50,7 +50,7 @@ PEAK = {"fp64": PEAK_FP64_TFLOPS, "fp32": PEAK_FP32_TFLOPS, "fp32_3m": PEAK_FP32
 # per-dispatch counters, their copy-kernel scale factors and the sha256 of
 # the kernel's sources at the time; the traffic is reported only while the
 # sources still hash to that value.
-TRAFFIC_SOURCES = ["engine_mfma.hip", "mfma_kernel.h", "mfma_tiles.h", "mfma_tree.h", "engine_common.h", "pm_internal.h"]
+TRAFFIC_SOURCES = ["engine_wave.hip", "wave_kernel.h", "wave_slices.h", "mfma_wave.h", "engine_common.h", "pm_internal.h"]
 TRAFFIC_PROFILE = "profiles/propagate_d16_random_qudit_traffic.md"
 LEGS = ["precisions", "slices", "d64", "small", "chebyshev", "cf4", "trajectory", "grad", "grape", "batch", "cpu",
         "fixed_error", "magnus6"]
@@ -60,16 +60,26 @@ def taylor_products(m: int) -> int:
     return 0 if m <= 1 else (1 if m == 2 else m // 2 + 1)
 
 
+def series_products(m: int, precision: int, d: int) -> int:
+    """Products of the degree-m series: the FP64 tile engines (d > 4) evaluate
+    it in blocks of three powers, degree 1, 2, 4, 6, 9, 12, 15 in 0..6 products;
+    the others by the cos / sin split."""
+    if precision == 0 and d > 4:
+        return next((q for q, deg in enumerate((1, 2, 4, 6, 9, 12, 15)) if deg >= m), 6)
+    return taylor_products(m)
+
+
 def engine_dim(d: int) -> int:
     return d if d <= 4 else (16 if d <= 16 else (32 if d <= 32 else 64))
 
 
 def algorithmic_flops(pm, w, precision, n_leaves: int) -> float:
     """Flops the kernel's algorithm needs for one propagation: per slice
-    8 d^3 per complex product over the Taylor products (Y powers and G S'),
+    8 d^3 per complex product over the series' products (series_products),
     the s squarings and the chain product, plus 4 M d^2 for the expand; the
     tree adds (n_leaves - 1) products.  (m, s) per slice come from the
-    library's planner on ||G_j||_1."""
+    library's planner on ||G_j||_1 (FP64 above dimension 4: an upper bound, the
+    engines plan by a bound of the 2-norm)."""
     D = engine_dim(w.dim)
     B, _ = pm.build_basis_host(w.H0, w.Hk, w.order)
     M = B.shape[0]
@@ -97,7 +107,7 @@ def algorithmic_flops(pm, w, precision, n_leaves: int) -> float:
         nu = np.max(np.sum(np.abs(G), axis=1), axis=1)
         for x in nu:
             m, s = pm.plan_expm(float(x), precision, n_slices=n)
-            prods += taylor_products(m) + s + 1
+            prods += series_products(m, precision, w.dim) + s + 1
     prods += n_leaves - 1
     return 8.0 * D ** 3 * prods + 4.0 * M * D * D * n
 

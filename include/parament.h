@@ -173,7 +173,8 @@ pm_status pm_equiprop_dev(pm_ctx *ctx, const double *samples_dev,
  * pm_set_hamiltonian, and the caller's buffers are used as given).  A
  * propagation whose tree needs more than the array (4 KiB per tree node at
  * dimensions 5..16, 16 KiB at 17..32, 64 KiB at 33..64; about
- * 2 * chains / 4 + 64 nodes at 5..16 and 2 * chains + 64 above) returns
+ * 2 * chains / 4 + 64 nodes up to 16 (PM_FP64: up to 32) and 2 * chains + 64
+ * above) returns
  * PM_E_INVALID_ARG; longer chains (pm_set_chunk) shrink the tree.  The
  * array is shared by every call on a device and keeps the last call's
  * contents; its tickets are cleared on `stream` (by a fill kernel) before
@@ -319,7 +320,9 @@ pm_status pm_tuning_set(const char *key, int dim_class, int precision, int64_t v
  * number of squarings for every slice (the degree is then the smallest that
  * meets the precision's threshold, or the cap), -1 restores automatic choice.
  * chunk > 0 fixes how many consecutive slices one wave team multiplies before
- * the tree, 0 restores the automatic choice. */
+ * the tree, 0 restores the automatic choice.  Dimensions 1..4 round it up: to
+ * 1024 slices in the reduced precisions, in PM_FP64 to 128 (dimensions 1, 2) or
+ * 64, as long as that is at most one chain per resident wave (else 1024). */
 pm_status pm_set_expm_policy(pm_ctx *ctx, int max_taylor_degree, int force_s);
 pm_status pm_set_chunk(pm_ctx *ctx, int64_t chunk);
 
@@ -478,7 +481,10 @@ pm_status pm_plan_chebyshev(double nu, int precision, int max_degree, int force_
 /* The planner's choice for a slice with ||G||_1 = nu in a propagation of
  * n_slices slices: Taylor degree m and squarings s minimising the product
  * count (ties to the smaller s), subject to nu / 2^s <= theta_m and
- * m <= max_degree. */
+ * m <= max_degree.  The reduced precisions' engines and the 64-level gradient
+ * follow it; PM_FP64 propagations above dimension 4 take degrees 1, 2, 4, 6, 9,
+ * 12 or 15 (one product more each) from a bound of the exponent's 2-norm, at
+ * most max_degree and at a truncation target no looser than this one. */
 pm_status pm_plan_expm(double nu, int precision, int max_degree, int64_t n_slices,
                        int *m_out, int *s_out);
 

@@ -269,8 +269,8 @@ __device__ __forceinline__ Strip<NT> strip_expm1(const PropParams& p, const Stri
     return E;
 }
 
-// exp(i G) - I by the degree-m Chebyshev series of cheb_parts on the interval
-// [-theta, theta]: C + i P with C = sum e_i T_i(Y) and P = X sum b_i T_i(Y),
+// exp(i G) - I by the degree-m Chebyshev series on the interval [-theta, theta],
+// split into its even and odd halves: C + i P with C = sum e_i T_i(Y) and P = X sum b_i T_i(Y),
 // X = G / theta, Y = 2 X^2 - I; `ec` the degree's row of even and odd
 // coefficients.
 template <int NT, int KS>
