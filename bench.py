@@ -670,7 +670,7 @@ def main():
                      "frac": ach64 / PEAK_FP64_TFLOPS, "traffic": headline_traffic(),
                      "traffic_unit": "bytes per launch", "traffic_profile": TRAFFIC_PROFILE,
                      "algorithmic_bytes_per_launch": w.samples.size * 8 + d * d * 16,
-                     "kernel": "propagate_mfma<double,16,4,true,0,false,false,false>", "kernel_ms": k64,
+                     "kernel": "propagate_wave<Wide<1,4>,0,false,true>", "kernel_ms": k64,
                      "algorithmic_flop_per_launch": flops["fp64"],
                      "frac_basis": "algorithmic flops: 8 d^3 per complex product",
                      "issued_mfma_flop_per_launch": issued64,
