@@ -483,8 +483,9 @@ pm_status pm_plan_chebyshev(double nu, int precision, int max_degree, int force_
  * count (ties to the smaller s), subject to nu / 2^s <= theta_m and
  * m <= max_degree.  The reduced precisions' engines and the 64-level gradient
  * follow it; PM_FP64 propagations above dimension 4 take degrees 1, 2, 4, 6, 9,
- * 12 or 15 (one product more each) from a bound of the exponent's 2-norm, at
- * most max_degree and at a truncation target no looser than this one. */
+ * 12, 15, 18 or 21 (one product more each) from a bound of the exponent's
+ * 2-norm, at most max_degree and at a truncation target no looser than this
+ * one. */
 pm_status pm_plan_expm(double nu, int precision, int max_degree, int64_t n_slices,
                        int *m_out, int *s_out);
 

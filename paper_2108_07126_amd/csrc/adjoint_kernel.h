@@ -209,7 +209,7 @@ __attribute__((amdgpu_waves_per_eu(S::NT == 1 ? 2 : 1, S::NT == 1 ? 8 : 1))) adj
             z = fmin(z, 2.0 * mx_norm1<S>(G));
             ok = __ballot(z <= lth);
             if (!ok) {
-                s = wave_uniform(min(min_squarings(0.5 * z, p.sth[p.qmax]), 62));
+                s = wave_uniform(min(min_squarings(0.5 * z, fmin(p.sth[p.qmax], 1.0)), 62));
                 const double sc = ldexp(1.0, -s);
                 z *= sc;
                 mx_each<S>([&](int e) {
@@ -239,7 +239,8 @@ __attribute__((amdgpu_waves_per_eu(S::NT == 1 ? 2 : 1, S::NT == 1 ? 8 : 1))) adj
             auto conj_by = [&](const Mx<S>& E, const Mx<S>& X) {   // V X V^H of a Hermitian X
                 return mx_apply<S>(E, mx_adjoint<S>(mx_apply<S>(E, X), sl.scr, L));
             };
-            Mx<S> E = mx_expm1<S>(p, G, p.qmax, L);
+            const int sq = plan_scheme(0.5 * z, lane_sth_of(p, L.lane));
+            Mx<S> E = mx_expm1<S>(p, G, wave_uniform(sq < 0 ? p.qmax : sq), L);
             for (int q = 0; q < s; ++q) {
                 const Mx<S> C = conj_by(E, Psi);
                 mx_each<S>([&](int e) {

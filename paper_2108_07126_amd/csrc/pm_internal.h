@@ -24,9 +24,11 @@ constexpr int kFanInLog2 = 3;
 
 // Evaluation schemes of the series exp(i G) on the tile engines (powers in
 // blocks of three, Paterson-Stockmeyer): scheme q takes q products and
-// reaches degree 1, 2, 4, 6, 9, 12, 15.
-constexpr int kSchemes = 7;
+// reaches degree 1, 2, 4, 6, 9, 12, 15, 18, 21 (the largest cap, which forced
+// squarings may need).
+constexpr int kSchemes = 9;
 constexpr int scheme_degree(int q) { return q < 2 ? q + 1 : (q == 2 ? 4 : 3 * (q - 1)); }
+static_assert(scheme_degree(kSchemes - 1) == PM_MAX_TAYLOR_DEGREE, "every degree cap is reached");
 
 // Basis matrices of the one-wave teams' basis form: their weights fill a row of
 // 16 lanes, and in LDS they leave room for two blocks per CU at D = 16.
