@@ -204,7 +204,9 @@ propagate_strip(PropParams p) {
         } else {
             G = strip_diagonal<NT>(L, 0.0);
             strip_add<NT>(Q, strip_mul<NT, KS>(se, Q, L, [&](int f) { ex.piece(G, wl, f); }));
-            ex.piece(G, wl, RT * RT);
+            // (waves past the row tiles form no product, so no piece was loaded
+            // for them: their strip of G stays zero, as the 1-norm takes it)
+            if (L.c < RT) ex.piece(G, wl, RT * RT);
             ex.rest(G, wl, RT);
         }
     }
