@@ -212,16 +212,21 @@ __device__ __forceinline__ float wave_sum_f(float x) {
     return (a + b) + (c + d);
 }
 
+// A term's part in a bound of the exponent's norm, |w_m| ||B_m||_2.  The product is
+// formed in FP64: in units where h or a commutator leaves the range of FP32
+// (joules over hbar: w = 1e46, ||B|| = 1e-48) the term itself is of order one.
+__device__ __forceinline__ float term_bound(double w, double beta) { return (float)(fabs(w) * beta); }
+
 // Upper bound of ||G_j||_2 <= sum_m |w_m| ||B_m||_2 from the lanes' weights
 // (lane m holds weight m and beta_m, zero past the basis).  The 1-norm of the
 // formed exponent, the planner's bound before, is larger for a dense G (by
 // up to sqrt(d): 4 times on 64-level GUE systems) and costs a matrix of
 // square roots, row sums and, on several waves, barriers.
-__device__ __forceinline__ double spectral_bound(double w, float beta) {
-    return (double)(wave_sum_f(fabsf((float)w) * beta) * (1.0f + 0x1p-18f));
+__device__ __forceinline__ double spectral_bound(double w, double beta) {
+    return (double)(wave_sum_f(term_bound(w, beta)) * (1.0f + 0x1p-18f));
 }
 
-__device__ __forceinline__ float lane_beta_of(const PropParams& p, int m) { return m < p.M ? p.beta[m] : 0.0f; }
+__device__ __forceinline__ double lane_beta_of(const PropParams& p, int m) { return m < p.M ? p.beta[m] : 0.0; }
 
 __device__ __forceinline__ double lane_sth_of(const PropParams& p, int lane) {
     return lane < kSchemes ? p.sth[lane] : -1.0;
@@ -385,8 +390,8 @@ __device__ __forceinline__ double m6_weight(const PropParams& p, const WeightRec
 // Upper bound of the sixth-order exponent's 2-norm from the moments'
 // bounds p_i = sum |w| beta (lane 16 q + m holds a weight of moment q + 1):
 // ||R1|| <= 2 p1 p2, ||R2|| <= (1/30) p1 (2 p3 + r1), and the outer commutator.
-__device__ __forceinline__ double m6_bound(double w, float beta) {
-    const float t = row16_sum_f(fabsf((float)w) * beta);
+__device__ __forceinline__ double m6_bound(double w, double beta) {
+    const float t = row16_sum_f(term_bound(w, beta));
     const float p1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 0));
     const float p2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 16));
     const float p3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 32));

@@ -101,7 +101,7 @@ propagate_strip(PropParams p) {
         if constexpr (M6) return m6_weight(p, wr, v);
         else return combine_weight(p, wr, v);
     };
-    const float beta = lane_beta_of(p, M6 ? (L.lane & 15) : L.lane);
+    const double beta = lane_beta_of(p, M6 ? (L.lane & 15) : L.lane);
     const double lsth = lane_sth_of(p, L.lane);
     const double lcth = lane_ctheta_of(p, L.lane);
     Strip<NT> Q = strip_diagonal<NT>(L, 1.0);

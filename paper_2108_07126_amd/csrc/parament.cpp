@@ -38,7 +38,7 @@ struct pm_ctx {
     pm::EngineInfo eng{};
     std::vector<double> basis;   // FP64 [M][dim][dim] interleaved
     std::vector<double> norms;   // [M]
-    std::vector<float> beta;     // [M] bounds of the 2-norms (tile engines)
+    std::vector<double> beta;    // [M] bounds of the 2-norms (tile engines)
     uint8_t pair_a[pm::kMaxBasis] = {};
     uint8_t pair_b[pm::kMaxBasis] = {};
     double theta[pm::kMaxDeg + 1] = {};
@@ -354,9 +354,9 @@ double norm1(const Mat& a, int64_t d) {
 // is within d^(1/2n) of the 2-norm (9 % at d = 16, 30 % at d = 64, a third of
 // that for a GUE matrix).  Real and imaginary planes, so the inner loop is a
 // plain vector update.
-float norm2_bound(const Mat& a, int64_t d) {
+double norm2_bound(const Mat& a, int64_t d) {
     const double n1 = norm1(a, d);
-    if (!(n1 > 0.0)) return 0.0f;
+    if (!(n1 > 0.0)) return 0.0;
     const int squarings = d <= 32 ? 4 : 3;
     std::vector<double> xr((size_t)(d * d)), xi(xr.size()), yr(xr.size()), yi(xr.size());
     for (int64_t i = 0; i < d * d; ++i) {
@@ -387,7 +387,7 @@ float norm2_bound(const Mat& a, int64_t d) {
             ri[i] = 0.0;
         }
         f = std::sqrt(f);
-        if (!(f > 0.0)) return (float)(n1 * (1.0 + 1e-6));
+        if (!(f > 0.0)) return n1 * (1.0 + 1e-6);
         lg = 2.0 * lg + std::log(f);
         const double inv = 1.0 / f;
         for (int64_t i = 0; i < d * d; ++i) {
@@ -395,7 +395,7 @@ float norm2_bound(const Mat& a, int64_t d) {
             xi[i] = yi[i] * inv;
         }
     }
-    return (float)(std::min(n1, n1 * std::exp(lg / (1 << squarings))) * (1.0 + 1e-6));
+    return std::min(n1, n1 * std::exp(lg / (1 << squarings))) * (1.0 + 1e-6);
 }
 
 // The ordered basis: H0, H_1..H_K [, i[H0,H_k] (k=1..K), i[H_k,H_k'] (k<k')].
@@ -1396,7 +1396,7 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
     // precisions plan by the exponent's 1-norm)
     for (int m = 0; m < M; ++m)
         ctx->beta[m] = m <= n_ctrl && ctx->precision == PM_FP64 ? norm2_bound(basis[m], dim)
-                                                                : (float)(norms[m] * (1.0 + 1e-6));
+                                                                : norms[m] * (1.0 + 1e-6);
     std::memset(ctx->pair_a, 0, sizeof(ctx->pair_a));
     std::memset(ctx->pair_b, 0, sizeof(ctx->pair_b));
     for (size_t q = 0; q < pairs.size(); ++q) {

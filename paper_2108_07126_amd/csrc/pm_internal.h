@@ -58,7 +58,7 @@ struct PropParams {
     double sth[kSchemes];        // largest ||G||_2 for scheme q (-1: past the degree cap)
     int qmax;                    // the last available scheme
     double tc[scheme_degree(kSchemes - 1) + 1];   // 1/k!, zero past the degree cap
-    float beta[kMaxBasis];       // upper bounds of ||B_m||_2
+    double beta[kMaxBasis];      // upper bounds of ||B_m||_2
     int K, M, order, du;
     int max_degree, force_s;
     int basis_lds;               // MFMA engine: block keeps a copy of the basis in LDS

@@ -46,8 +46,8 @@ __device__ __forceinline__ double comm_weight(const PropParams& p, const WeightR
     return r.kind == 5 ? 0.0 : w;
 }
 
-__device__ __forceinline__ double comm_bound(double w, float beta) {
-    const float t = row16_sum_f(fabsf((float)w) * beta);
+__device__ __forceinline__ double comm_bound(double w, double beta) {
+    const float t = row16_sum_f(term_bound(w, beta));
     const float s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 0));
     const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 16));
     const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 32));
@@ -86,8 +86,7 @@ struct WaveSlices {
     bool second;             // Pair: this lane's column lies in the second matrix
     int64_t wbase, wend, jlast;
     WeightRecipe wr;
-    float beta;
-    double lsth, wl;
+    double beta, lsth, wl;
     SliceSamples smp;
     float bounds;            // of the row's slice
     double bound;            // of this step's slice (Pair: the larger), once planned
@@ -109,7 +108,9 @@ struct WaveSlices {
         if constexpr (EXPO == EXPO_M6) wr = m6_recipe(p, L.lane);
         else if constexpr (EXPO == EXPO_COMM) wr = comm_recipe(p, L.lane);
         else wr = weight_recipe(p, wlane);
-        beta = wlane < nb ? p.beta[wlane] : 0.0f;
+        beta = wlane < nb ? p.beta[wlane] : 0.0;
+        // (the commutator's factors share its h^2, so that neither bound leaves FP32)
+        if constexpr (EXPO == EXPO_COMM) beta *= row == 1 ? p.h : (row == 2 ? 1.0 / p.h : 1.0);
         lsth = lane_sth_of(p, kRows ? wlane : L.lane);
         wl = 0.0;
         bounds = 0.0f;
@@ -163,7 +164,7 @@ struct WaveSlices {
             if (kRows && wbase + wstep + t >= wend) wl = 0.0;
             smp = gather(t + (kRows ? kGroup : 1));
             if constexpr (kRows) {
-                bounds = row16_sum_f(fabsf((float)wl) * beta) * (1.0f + 0x1p-18f);
+                bounds = row16_sum_f(term_bound(wl, beta)) * (1.0f + 0x1p-18f);
                 fits = __ballot((double)bounds <= lsth);
                 wave_lds_fence();
                 lw[L.lane] = wl;

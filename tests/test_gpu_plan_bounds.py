@@ -37,3 +37,40 @@ def test_own_norm_where_terms_cancel(pm, d, scale):
             ctx.set_expm_policy(force_s=force)
             out.append(ctx.equiprop(w.samples, w.h, return_slices=True))
     assert np.array_equal(out[0][1], out[1][1]) and np.array_equal(out[0][0], out[1][0])
+
+
+@pytest.mark.parametrize("d,K", [(3, 2), (5, 2), (8, 3), (8, 5), (12, 2), (16, 5), (24, 2), (32, 4), (40, 2), (64, 2)])
+@pytest.mark.parametrize("e", [80, -80])
+def test_units(pm, d, K, e):
+    """The Hamiltonian in other units: scaled by 2^-e, the slice width by 2^e (e = 80
+    is joules and seconds over hbar), every exponent is the same number, so every
+    plan and every result is too, bit for bit.  The controls rest over the first
+    half of a chain: its bound is small, the second half's is not."""
+    import torch
+    rng = np.random.default_rng(d)
+    V = torch.from_numpy(rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d))).cuda()
+    for order in (2, 4, orc.CF4, 6):
+        w = synth.random_system(d, K, n_slices=11, h=0.4, order=order, tag=1120)
+        w.samples[:, : w.samples.shape[1] * 6 // 11] = 0.0
+        out = []
+        for x in (0, e):
+            print(f"[case] units d={d} K={K} order={order} 2^{x}", file=sys.stderr, flush=True)
+            with pm.Context(0, pm.PM_FP64) as ctx:
+                ctx.set_hamiltonian(w.H0 * 1e-3 * 2.0 ** -x, w.Hk * 2.0 ** -x, order)
+                ctx.set_chunk(12)
+                h = w.h * 2.0 ** x
+                res = [ctx.equiprop(w.samples, h)]
+                if order in (2, 4):
+                    res.append(ctx.equiprop(w.samples, h, return_slices=True)[1])
+                if order != 6:
+                    res.append(ctx.trajectory(w.samples, h))
+                    c = torch.from_numpy(w.samples).cuda()
+                    g = torch.zeros_like(c)
+                    ctx.backward_dev(c, h, V, g)
+                    torch.cuda.synchronize()
+                    res.append(g.cpu().numpy())
+            out.append(res)
+        Uo = orc.propagate(w.H0 * 1e-3, w.Hk, w.samples, w.h, order)
+        assert orc.relative_frobenius(out[1][0], Uo) <= 1e-10, order
+        for a, b in zip(*out):
+            assert np.array_equal(a, b), order
