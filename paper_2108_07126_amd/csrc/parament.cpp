@@ -909,12 +909,15 @@ pm_status launch_grad(pm_ctx* ctx, const double* d_samples, int64_t n_samples, d
     gp.UT = p.U_out;   // where the forward left U(T)
     gp.gw = ctx->d_gw;
     // few long chains: split each (pairs: each half) into parts of at least
-    // four slices until about a wave per SIMD runs; a part recomputes its
+    // four slices until the device is full; a part recomputes its
     // predecessors in the chain, and shorter parts lose more to that than
-    // they gain
+    // they gain.  Full is a wave per SIMD up to 32 levels, and one of the
+    // 64-wide kernel's blocks (135 KB of LDS) per CU: parts past that only
+    // recompute (64 levels: with 2048 units 7.2 ms for 4096 slices and 39.6 ms
+    // for 16384, with one unit per CU 4.5 and 16.9 ms)
     gp.split = 1;
     gp.grad_direct = nullptr;
-    const int64_t max_units = e.D <= 32 ? 1024 : 2048, run = p.pair ? (p.chunk + 1) / 2 : p.chunk;
+    const int64_t max_units = e.D <= 32 ? 1024 : ctx->n_cu, run = p.pair ? (p.chunk + 1) / 2 : p.chunk;
     while (p.n_chains * gp.split * 2 <= max_units && run >= 8 * gp.split) gp.split *= 2;
     fill_adjoint(gp);
     he = pm::launch_backward(e.D, gp, d_grad, stream);
