@@ -229,8 +229,8 @@ hipError_t launch_strip_one(const PropParams& p, hipStream_t stream) {
 }
 
 // The Taylor series of orders 2, 4 and CF4 over the k-slices the dimension
-// reaches, in steps of two; the Chebyshev series and the sixth-order scheme
-// over all of them.
+// reaches, in steps of two; the Chebyshev series over three quarters or all of
+// them, the sixth-order scheme over all.
 template <int D, int KS>
 hipError_t launch_strip_ks(const PropParams& p, hipStream_t stream) {
     if constexpr (KS < D / 4) {
@@ -244,7 +244,9 @@ hipError_t launch_strip_d(const PropParams& p, hipStream_t stream) {
     const bool ch = p.method == PM_EXPM_CHEBYSHEV;
     if (p.order == kOrderM6)
         return ch ? launch_strip_one<D, D / 4, true, true>(p, stream) : launch_strip_one<D, D / 4, false, true>(p, stream);
-    if (ch) return launch_strip_one<D, D / 4, true, false>(p, stream);
+    if (ch)
+        return p.du <= 3 * D / 4 ? launch_strip_one<D, 3 * D / 16, true, false>(p, stream)
+                                 : launch_strip_one<D, D / 4, true, false>(p, stream);
     return launch_strip_ks<D, D / 8 + 2>(p, stream);
 }
 

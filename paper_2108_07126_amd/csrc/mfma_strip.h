@@ -298,16 +298,20 @@ __device__ __forceinline__ Strip<NT> strip_cheb(const Strip<NT>& G, int m, doubl
         add(C, ec[1], Tc);
         if (qs >= 1) add(Sp, eb[1], Tc);
         if (qc >= 2) s = strip_put<NT>(sl, Tc, L);
-        for (int i = 2; i <= qc; ++i) {
-            Strip<NT> Tn = strip_mul<NT, KS>(s, Tc, L);
+        // T_i over T_{i-2}, in turns (no copies, no third strip)
+        auto next = [&](int i, const Strip<NT>& T1, Strip<NT>& Tn) {
+            const Strip<NT> Z = strip_mul<NT, KS>(s, T1, L);
             strip_each<NT>([&](int k, int r) {
-                Tn.t[k].re[r] = fma(2.0, Tn.t[k].re[r], -Tm.t[k].re[r]);
-                Tn.t[k].im[r] = fma(2.0, Tn.t[k].im[r], -Tm.t[k].im[r]);
+                Tn.t[k].re[r] = fma(2.0, Z.t[k].re[r], -Tn.t[k].re[r]);
+                Tn.t[k].im[r] = fma(2.0, Z.t[k].im[r], -Tn.t[k].im[r]);
             });
             add(C, ec[i], Tn);
             if (i <= qs) add(Sp, eb[i], Tn);
-            Tm = Tc;
-            Tc = Tn;
+        };
+        for (int i = 2; i <= qc; i += 2) {
+            next(i, Tc, Tm);
+            if (i == qc) break;
+            next(i + 1, Tm, Tc);
         }
     }
     Strip<NT> P;

@@ -240,6 +240,26 @@ __device__ __forceinline__ Mx<S> mx_expm1(const PropParams& p, const Mx<S>& G, i
     return E;
 }
 
+typedef double d2_t __attribute__((ext_vector_type(2)));
+
+// A matrix put aside in LDS, the lane's entries as they are, and taken back.  (The
+// compiler must not carry them over in registers after all.)
+template <class S>
+constexpr int mx_aside_entries() { return 64 * S::kRegs; }
+template <class S>
+__device__ __forceinline__ void mx_put_aside(d2_t* to, const Mx<S>& X, const WLane& L) {
+    mx_each<S>([&](int e) { to[e * 64 + L.lane] = d2_t{X.re[e], X.im[e]}; });
+    asm volatile("" ::: "memory");
+}
+template <class S>
+__device__ __forceinline__ void mx_take_back(Mx<S>& X, const d2_t* from, const WLane& L) {
+    mx_each<S>([&](int e) {
+        const d2_t v = from[e * 64 + L.lane];
+        X.re[e] = v.x;
+        X.im[e] = v.y;
+    });
+}
+
 // exp(i G) - I by the degree-m Chebyshev series on the interval
 // [-theta, theta], the spectrum's bound (eq. chebychev_series with
 // alpha = -theta, beta = theta), split into its even and odd halves.  With
@@ -250,9 +270,11 @@ __device__ __forceinline__ Mx<S> mx_expm1(const PropParams& p, const Mx<S>& G, i
 // e_0 = J_0, e_i = 2 (-1)^i J_2i, and b the alternating suffix sums of the
 // odd coefficients (`ec`: the degree's row of e, then of b, kChebHalf each).
 // floor(m/2) + 1 products, all with a Hermitian left factor, where the
-// Clenshaw recurrence in X takes m.
+// Clenshaw recurrence in X takes m.  Two tiles wide X waits in LDS (`aside`):
+// besides it the series holds six matrices of 64 registers.
 template <class S>
-__device__ __forceinline__ Mx<S> mx_cheb(const Mx<S>& G, int m, double theta, const double* ec, const WLane& L) {
+__device__ __forceinline__ Mx<S> mx_cheb(const Mx<S>& G, int m, double theta, const double* ec, d2_t* aside,
+                                         const WLane& L) {
     const double inv = 1.0 / theta;
     const double* eb = ec + kChebHalf;
     const int qc = m / 2, qs = (m - 1) / 2;
@@ -267,6 +289,7 @@ __device__ __forceinline__ Mx<S> mx_cheb(const Mx<S>& G, int m, double theta, co
             A.im[e] = fma(c, B.im[e], A.im[e]);
         });
     };
+    if constexpr (S::NT > 1) mx_put_aside<S>(aside, X, L);
     if (qc >= 1) {
         Mx<S> Y = mx_mul<S>(X, X), Tm = mx_diagonal<S>(L, 1.0);
         mx_each<S>([&](int e) {
@@ -275,20 +298,25 @@ __device__ __forceinline__ Mx<S> mx_cheb(const Mx<S>& G, int m, double theta, co
         });
         add(C, ec[1], Y);
         if (qs >= 1) add(Sp, eb[1], Y);
-        Mx<S> Tc = Y;
-        for (int i = 2; i <= qc; ++i) {
-            Mx<S> Tn = mx_mul<S>(Y, Tc);
+        // T_i over T_{i-2}, in turns (no copies, no third matrix)
+        auto next = [&](int i, const Mx<S>& Tc, Mx<S>& Tn) {
+            const Mx<S> Z = mx_mul<S>(Y, Tc);
             mx_each<S>([&](int e) {
-                Tn.re[e] = fma(2.0, Tn.re[e], -Tm.re[e]);
-                Tn.im[e] = fma(2.0, Tn.im[e], -Tm.im[e]);
+                Tn.re[e] = fma(2.0, Z.re[e], -Tn.re[e]);
+                Tn.im[e] = fma(2.0, Z.im[e], -Tn.im[e]);
             });
             add(C, ec[i], Tn);
             if (i <= qs) add(Sp, eb[i], Tn);
-            Tm = Tc;
-            Tc = Tn;
+        };
+        Mx<S> Tc = Y;
+        for (int i = 2; i <= qc; i += 2) {
+            next(i, Tc, Tm);
+            if (i == qc) break;
+            next(i + 1, Tm, Tc);
         }
     }
     Mx<S> P;
+    if constexpr (S::NT > 1) mx_take_back<S>(X, aside, L);
     if (qs >= 1) {
         P = mx_mul<S>(X, Sp);
     } else {
@@ -303,8 +331,6 @@ __device__ __forceinline__ Mx<S> mx_cheb(const Mx<S>& G, int m, double theta, co
     });
     return C;
 }
-
-typedef double d2_t __attribute__((ext_vector_type(2)));
 
 // Order this wave's LDS writes before its reads of other lanes' entries (and
 // the reverse).

@@ -42,11 +42,16 @@ __attribute__((amdgpu_waves_per_eu(S::NT == 1 ? 2 : 1, S::NT == 1 ? 8 : 1))) pro
     const int64_t jm = S::kPair ? j0 + (j1 - j0 + 1) / 2 : j1;
     const int64_t steps = jm - j0;
     const double lcth = lane_ctheta_of(p, L.lane);
+    // Chebyshev, two tiles wide: LDS for two matrices put aside, X and Q
+    constexpr bool kAside = CH && S::NT > 1;
+    d2_t* aside = reinterpret_cast<d2_t*>(wsm + 2 + wave_run_bytes<S::NT>(sl.nb, BL) / 8) +
+                  team * 2 * mx_aside_entries<S>();
     Mx<S> Q = mx_diagonal<S>(L, 1.0);
     sl.start(j0, jm, jm, j1);
     for (int64_t t = 0; t < steps; ++t) {
         Mx<S> E;
         if constexpr (CH) {
+            if constexpr (kAside) mx_put_aside<S>(aside + mx_aside_entries<S>(), Q, L);
             Mx<S> G = sl.exponent(t);
             int m, s;
             plan_cheb_lanes(p, wave_uniform(mx_norm1<S>(G)), L.lane, lcth, m, s);
@@ -57,8 +62,9 @@ __attribute__((amdgpu_waves_per_eu(S::NT == 1 ? 2 : 1, S::NT == 1 ? 8 : 1))) pro
                 G.re[e] *= sc;
                 G.im[e] *= sc;
             });
-            E = mx_cheb<S>(G, m, p.ctheta[m], p.cheb_j + kChebSplitOffset + m * 2 * kChebHalf, L);
+            E = mx_cheb<S>(G, m, p.ctheta[m], p.cheb_j + kChebSplitOffset + m * 2 * kChebHalf, aside, L);
             if (s > 0) mx_square<S>(E, s, sl.scr, L);
+            if constexpr (kAside) mx_take_back<S>(Q, aside + mx_aside_entries<S>(), L);
         } else {
             E = sl.slice(t);
         }
@@ -121,11 +127,11 @@ __attribute__((amdgpu_waves_per_eu(S::NT == 1 ? 2 : 1, S::NT == 1 ? 8 : 1))) pro
     mx_tree<Node>(p, blockIdx.x, N, team, slots, tick, L);
 }
 
-// LDS of a launch: a ticket, then the run's part or the handover slots of the
-// end, whichever is larger.
+// LDS of a launch: a ticket, then the run's part (with `aside` two matrices more
+// per team) or the handover slots of the end, whichever is larger.
 template <int NT>
-constexpr size_t wave_lds_bytes(int nb, bool bl) {
-    const size_t run = wave_run_bytes<NT>(nb, bl), end = (size_t)kWaveTeams * mx_slot_entries<Wide<NT, 4>>() * 16;
+constexpr size_t wave_lds_bytes(int nb, bool bl, bool aside = false) {
+    const size_t run = wave_run_bytes<NT>(nb, bl) + (aside ? (size_t)kWaveTeams * 2 * NT * NT * 4096 : 0), end = (size_t)kWaveTeams * mx_slot_entries<Wide<NT, 4>>() * 16;
     return 16 + (run > end ? run : end);
 }
 
@@ -140,7 +146,7 @@ hipError_t launch_wave_one(const PropParams& p, hipStream_t stream) {
         attr_set = true;
     }
     hipLaunchKernelGGL((propagate_wave<S, EXPO, CH, BL>), dim3((unsigned)p.n_leaves), dim3(64 * kWaveTeams),
-                       wave_lds_bytes<S::NT>(nb, BL), stream, p);
+                       wave_lds_bytes<S::NT>(nb, BL, CH && S::NT > 1), stream, p);
     return hipGetLastError();
 }
 
