@@ -85,7 +85,7 @@ __device__ __forceinline__ Mx<S> chain_start(const PropParams& p, int64_t leaf, 
         for (int i = lo + 1; i < hi; ++i) {
             const Mx<Node> cur = A;
             if (i + 1 < hi) A = mx_node_load<Node, true>(node(i + 1), L);
-            P = mx_mul<Node>(cur, P);
+            P = mx_join<Node>(cur, P, L);
         }
     }
     mx_combine<Node>(P, team, kWaveTeams, slots, L);
@@ -102,8 +102,8 @@ __device__ __forceinline__ Mx<S> chain_start(const PropParams& p, int64_t leaf, 
     if (chain < p.n_chains) {
         for (int64_t c = leaf * kWaveTeams; c < chain; ++c) {
             const double* rec = p.chain_out + c * NN;
-            if constexpr (S::kPair) R = mx_mul<S>(pair_record_adj<S>(rec, L), R);
-            else R = mx_mul<S>(mx_node_load<S, true>(rec, L), R);
+            if constexpr (S::kPair) R = mx_join<S>(pair_record_adj<S>(rec, L), R, L);
+            else R = mx_join<S>(mx_node_load<S, true>(rec, L), R, L);
         }
         if constexpr (S::kPair) {
             // the second half starts after the first
@@ -113,7 +113,7 @@ __device__ __forceinline__ Mx<S> chain_start(const PropParams& p, int64_t leaf, 
                 A.re[e] = hi8 ? A.re[e] : (mx_diag<S>(L, e) ? 1.0 : 0.0);
                 A.im[e] = hi8 ? A.im[e] : 0.0;
             });
-            R = mx_mul<S>(A, R);
+            R = mx_join<S>(A, R, L);
         }
     }
     return R;

@@ -411,6 +411,14 @@ __device__ __forceinline__ Strip<NT> strip_node_load_adj(const double* node, con
     return Q;
 }
 
+// A node less the identity: the tree joins nodes as X + (A - I) X, which rounds
+// relative to ||A - I|| (mx_join in mfma_wave.h).
+template <int NT>
+__device__ __forceinline__ Strip<NT> strip_less_one(Strip<NT> A, const SLane& L) {
+    strip_each<NT>([&](int k, int r) { A.t[k].re[r] -= strip_diag(L, k, r) ? 1.0 : 0.0; });
+    return A;
+}
+
 // Root product into U_out.
 template <int NT>
 __device__ __forceinline__ void strip_store_root(const PropParams& p, const Strip<NT>& Q, const SLane& L) {
@@ -465,21 +473,22 @@ __device__ void strip_tree(const PropParams& p, int64_t leaf, Strip<NT> Q, const
                 char* s = sl.next();
                 if (active) {
                     if (idx == first) {
-                        strip_stage<NT>(s, strip_node_load_adj<NT>(p.nodes + (off + first + 1) * NN, L), L);
+                        strip_stage<NT>(s, strip_less_one<NT>(strip_node_load_adj<NT>(p.nodes + (off + first + 1) * NN, L), L), L);
                     } else {
-                        strip_stage_adj<NT>(s, Q, L);
+                        strip_stage_adj<NT>(s, strip_less_one<NT>(Q, L), L);
                         Q = strip_node_load<NT>(p.nodes + (off + first) * NN, L);
                     }
                 }
                 __syncthreads();
-                if (active) Q = strip_mul<NT, KS>(s, Q, L);
+                if (active) strip_add<NT>(Q, strip_mul<NT, KS>(s, Q, L));
             } else {
                 if (active) Q = strip_node_load<NT>(p.nodes + (off + first) * NN, L);
                 for (int64_t k = first + 1; k < first + members; ++k) {
                     char* s = sl.next();
-                    if (active) strip_stage<NT>(s, strip_node_load_adj<NT>(p.nodes + (off + k) * NN, L), L);
+                    if (active)
+                        strip_stage<NT>(s, strip_less_one<NT>(strip_node_load_adj<NT>(p.nodes + (off + k) * NN, L), L), L);
                     __syncthreads();
-                    if (active) Q = strip_mul<NT, KS>(s, Q, L);
+                    if (active) strip_add<NT>(Q, strip_mul<NT, KS>(s, Q, L));
                 }
             }
         }

@@ -176,6 +176,26 @@ __device__ __forceinline__ Mx<S> mx_apply(const Mx<S>& A, const Mx<S>& X) {
     return y;
 }
 
+// A^H X of unitary A (a chain's or a node's adjoint) as X + (A - I)^H X: the
+// product rounds relative to ||A - I||, which is small where chains are short and
+// the tree takes over their products (a full product rounds ten times as much).
+// 27 levels, 278 slices: gradient 1.1e-14 -> 4.0e-15, U(T) 8.0e-15 -> 1.5e-15.
+template <class S>
+__device__ __forceinline__ Mx<S> mx_join(Mx<S> A, const Mx<S>& X, const WLane& L) {
+    mx_each<S>([&](int e) { A.re[e] -= mx_diag<S>(L, e) ? 1.0 : 0.0; });
+    return mx_apply<S>(A, X);
+}
+
+// The tree's product.  Chains of one tile hold at least four slices, and few of
+// their products are the tree's: the full product rounds no worse than the chains
+// and is a fiftieth of a short propagation faster (16 levels, 100 slices 18.0 against
+// 18.4 us).
+template <class S>
+__device__ __forceinline__ Mx<S> mx_node_mul(const Mx<S>& A, const Mx<S>& X, const WLane& L) {
+    if constexpr (S::NT > 1) return mx_join<S>(A, X, L);
+    else return mx_mul<S>(A, X);
+}
+
 // exp(i G) - I for the (pre-scaled) Hermitian G by evaluation scheme q
 // (scheme_degree(q); coefficients p.tc[k] = 1/k!, zero past the degree cap),
 // Paterson-Stockmeyer in blocks of three powers with Y = G G, Z = G Y:
@@ -517,7 +537,7 @@ __device__ __forceinline__ void mx_combine(Mx<S>& Q, int team, int live, d2_t* s
                 A.re[e] = v.x;
                 A.im[e] = -v.y;
             });
-            Q = mx_mul<S>(A, Q);
+            Q = mx_node_mul<S>(A, Q, L);
         }
     }
 }
@@ -555,7 +575,7 @@ __device__ void mx_tree(const PropParams& p, int64_t leaf, Mx<S>& Q, int team, d
             double* nd = p.nodes + (off + first + 2 * team) * NN;
             if (2 * team + 1 < members) {
                 const Mx<S> A = mx_node_fetch<S, true>(nd + NN, L);
-                Q = mx_mul<S>(A, mx_node_fetch<S, false>(nd, L));
+                Q = mx_node_mul<S>(A, mx_node_fetch<S, false>(nd, L), L);
             } else if (2 * team < members) {
                 Q = mx_node_fetch<S, false>(nd, L);
             }
