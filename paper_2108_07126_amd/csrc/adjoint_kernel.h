@@ -88,10 +88,12 @@ __device__ __forceinline__ Mx<S> chain_start(const PropParams& p, int64_t leaf, 
             P = mx_join<Node>(cur, P, L);
         }
     }
-    mx_combine<Node>(P, team, kWaveTeams, slots, L);
+    const Part<Node> B = mx_combine<Node>(P, team, kWaveTeams, slots, L);
     __syncthreads();
     constexpr int LD = 16 * S::NT + 1;
-    if (team == 0) mx_each<Node>([&](int e) { slots[Node::row(L, e) * LD + Node::col(L, e)] = d2_t{P.re[e], P.im[e]}; });
+    if (B.mine(team))
+#pragma unroll
+        for (int r = 0; r < 4; ++r) slots[B.row(L, team, r) * LD + B.col(L, team)] = d2_t{B.re[r], B.im[r]};
     __syncthreads();
     Mx<S> R;
     mx_each<S>([&](int e) {

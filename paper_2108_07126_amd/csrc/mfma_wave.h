@@ -471,20 +471,8 @@ __device__ __forceinline__ Mx<S> mx_node_load(const double* node, const WLane& L
     return Q;
 }
 
-// Nodes shared inside the launch travel as agent-scope atomic accesses
+// Nodes shared inside the launch are read as agent-scope atomic accesses
 // (node_store_coherent: why no fences are needed).
-template <class S>
-__device__ __forceinline__ void mx_node_publish(double* node, const Mx<S>& Q, const WLane& L) {
-    mx_each<S>([&](int e) {
-        double* o = node + (S::row(L, e) * (16 * S::NT) + S::col(L, e)) * 2;
-        __hip_atomic_store(o, Q.re[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(o + 1, Q.im[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    });
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 template <class S, bool ADJ>
 __device__ __forceinline__ Mx<S> mx_node_fetch(double* node, const WLane& L) {
     Mx<S> Q;
@@ -498,70 +486,190 @@ __device__ __forceinline__ Mx<S> mx_node_fetch(double* node, const WLane& L) {
     return Q;
 }
 
-// Root product into U_out.
-template <class S>
-__device__ __forceinline__ void mx_store_root(const PropParams& p, const Mx<S>& Q, const WLane& L) {
-    mx_each<S>([&](int e) {
-        const int row = S::row(L, e), col = S::col(L, e);
-        if (row < p.du && col < p.du) {
-            p.U_out[(row * p.du + col) * 2 + 0] = Q.re[e];
-            p.U_out[(row * p.du + col) * 2 + 1] = Q.im[e];
-        }
-    });
-}
-
-// Product of consecutive teams' matrices, team 0 the earliest: teams 1 and 3
-// hand theirs to 0 and 2 through LDS, then 2 to 0 (later on the left).  Teams
-// from `live` on hold nothing.  The block's four waves all call it.  slots:
-// four of D (D + 1) entries; the handed matrix is written by rows and read as
-// its adjoint, both without bank conflicts.
 constexpr int kWaveTeams = 4;
 template <class S>
 constexpr int mx_slot_entries() { return 16 * S::NT * (16 * S::NT + 1); }
 
+// A block's product as its waves hold it: one tile wide the whole of it in team 0,
+// two wide a tile in each team.
 template <class S>
-__device__ __forceinline__ void mx_combine(Mx<S>& Q, int team, int live, d2_t* slots, const WLane& L) {
-    constexpr int LD = 16 * S::NT + 1;
-    d2_t* own = slots + team * mx_slot_entries<S>();
+struct Part {
+    static_assert(S::NT == 1 || S::NT * S::NT == kWaveTeams, "a tile per team");
+    double re[4], im[4];
+    static __device__ __forceinline__ bool mine(int team) { return S::NT > 1 || team == 0; }
+    static __device__ __forceinline__ int row(const WLane& L, int team, int r) { return 16 * (S::NT > 1 ? team >> 1 : 0) + L.g + 4 * r; }
+    static __device__ __forceinline__ int col(const WLane& L, int team) { return 16 * (S::NT > 1 ? team & 1 : 0) + L.j; }
+};
+
+template <class S>
+__device__ __forceinline__ void part_store(double* node, const Part<S>& Q, int team, const WLane& L) {
+    d2_t* o = reinterpret_cast<d2_t*>(node);
 #pragma unroll
-    for (int st = 1; st < kWaveTeams; st <<= 1) {
-        __syncthreads();
-        if ((team & (2 * st - 1)) == st && team < live)
-            mx_each<S>([&](int e) { own[S::row(L, e) * LD + S::col(L, e)] = d2_t{Q.re[e], Q.im[e]}; });
-        __syncthreads();
-        if ((team & (2 * st - 1)) == 0 && team + st < live) {
-            const d2_t* later = slots + (team + st) * mx_slot_entries<S>();
-            Mx<S> A;
-            mx_each<S>([&](int e) {
-                const d2_t v = later[S::col(L, e) * LD + S::row(L, e)];
-                A.re[e] = v.x;
-                A.im[e] = -v.y;
-            });
-            Q = mx_node_mul<S>(A, Q, L);
+    for (int r = 0; r < 4; ++r) o[Q.row(L, team, r) * (16 * S::NT) + Q.col(L, team)] = d2_t{Q.re[r], Q.im[r]};
+}
+
+// Agent-scope atomic stores, complete when this returns.
+template <class S>
+__device__ __forceinline__ void part_publish(double* node, const Part<S>& Q, int team, const WLane& L) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        double* o = node + (Q.row(L, team, r) * (16 * S::NT) + Q.col(L, team)) * 2;
+        __hip_atomic_store(o, Q.re[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(o + 1, Q.im[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// Root product into U_out.
+template <class S>
+__device__ __forceinline__ void part_store_root(const PropParams& p, const Part<S>& Q, int team, const WLane& L) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = Q.row(L, team, r), col = Q.col(L, team);
+        if (row < p.du && col < p.du) {
+            p.U_out[(row * p.du + col) * 2 + 0] = Q.re[r];
+            p.U_out[(row * p.du + col) * 2 + 1] = Q.im[r];
         }
     }
 }
 
-// The ticketed product tree (fan-in kFanIn) of blocks of four one-wave teams,
-// which stay together into it: team 0 publishes the block's node and takes
-// its group's ticket; in the group's last arrival team w multiplies nodes
-// 2 w + 1 and 2 w, read straight from memory, and mx_combine does the rest:
-// three dependent products per level.
+// Tiles (i0, n) .. (i0 + NI - 1, n) of A X = X + (A - I) X (mx_join) for two
+// matrices in handover slots.
+template <class S, int NI>
+__device__ __forceinline__ void mx_slot_tiles(const d2_t* a, const d2_t* x, int i0, int n, Part<S> (&out)[NI],
+                                              const WLane& L) {
+    constexpr int LD = 16 * S::NT + 1, KS = S::KS;
+    double xr[KS], xp[KS], xm[KS];
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+        const d2_t v = x[(16 * (q >> 2) + L.g + 4 * (q & 3)) * LD + 16 * n + L.j];
+        xr[q] = v.x;
+        xp[q] = v.x + v.y;
+        xm[q] = v.y - v.x;
+    }
+#pragma unroll
+    for (int t = 0; t < NI; ++t) {
+        const int i = i0 + t;
+        double ar[KS], ai[KS], sd[KS];
+#pragma unroll
+        for (int q = 0; q < KS; ++q) {
+            const int row = 16 * (q >> 2) + L.g + 4 * (q & 3), col = 16 * i + L.j;
+            const d2_t v = a[col * LD + row];
+            ar[q] = v.x - (row == col ? 1.0 : 0.0);
+            ai[q] = -v.y;
+            sd[q] = ar[q] - ai[q];
+        }
+        d4_t kk = {0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < KS; ++q) kk = mfma16(sd[q], xr[q], kk);
+        d4_t re = kk, im = kk;
+#pragma unroll
+        for (int q = 0; q < KS; ++q) {
+            re = mfma16(ai[q], xp[q], re);
+            im = mfma16(ar[q], xm[q], im);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const d2_t v = x[(16 * i + L.g + 4 * r) * LD + 16 * n + L.j];
+            out[t].re[r] = re[r] + v.x;
+            out[t].im[r] = im[r] + v.y;
+        }
+    }
+}
+
+// Product of consecutive teams' matrices, team 0 the earliest (later on the left);
+// teams from `live` on hold nothing.  The block's four waves all call it.  slots:
+// four of D (D + 1) entries; a matrix is written by rows and read as its adjoint,
+// both without bank conflicts.
+// One tile wide, teams 1 and 3 hand theirs to 0 and 2, then 2 to 0.  Two tiles wide
+// a product takes one wave 2.6 us, so the idle ones share it: two waves a product
+// (a column of tiles each), then four (a tile each).  27 levels, 100 slices 59.7 ->
+// 49.5 us (a handover and two levels of the tree), 1000 slices 80.0 -> 65.6 us.
 template <class S>
-__device__ void mx_tree(const PropParams& p, int64_t leaf, Mx<S>& Q, int team, d2_t* slots, int* tick,
+__device__ __forceinline__ Part<S> mx_combine(Mx<S>& Q, int team, int live, d2_t* slots, const WLane& L) {
+    constexpr int LD = 16 * S::NT + 1;
+    d2_t* own = slots + team * mx_slot_entries<S>();
+    auto hand = [&]() { mx_each<S>([&](int e) { own[S::row(L, e) * LD + S::col(L, e)] = d2_t{Q.re[e], Q.im[e]}; }); };
+    Part<S> P;
+    if constexpr (S::NT == 1) {
+#pragma unroll
+        for (int st = 1; st < kWaveTeams; st <<= 1) {
+            __syncthreads();
+            if ((team & (2 * st - 1)) == st && team < live) hand();
+            __syncthreads();
+            if ((team & (2 * st - 1)) == 0 && team + st < live) {
+                const d2_t* later = slots + (team + st) * mx_slot_entries<S>();
+                Mx<S> A;
+                mx_each<S>([&](int e) {
+                    const d2_t v = later[S::col(L, e) * LD + S::row(L, e)];
+                    A.re[e] = v.x;
+                    A.im[e] = -v.y;
+                });
+                Q = mx_mul<S>(A, Q);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            P.re[r] = Q.re[r];
+            P.im[r] = Q.im[r];
+        }
+    } else {
+        constexpr int SE = mx_slot_entries<S>();
+        __syncthreads();
+        if (team < live) hand();
+        __syncthreads();
+        if (live > 2) {
+            const int pair = team & 2, n = team & 1;
+            Part<S> C[2];
+            if (pair + 1 < live) mx_slot_tiles<S, 2>(slots + (pair + 1) * SE, slots + pair * SE, 0, n, C, L);
+            __syncthreads();
+            if (pair + 1 < live)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        slots[pair * SE + (16 * i + L.g + 4 * r) * LD + 16 * n + L.j] = d2_t{C[i].re[r], C[i].im[r]};
+            __syncthreads();
+        }
+        if (live > 1) {
+            Part<S> C[1];
+            mx_slot_tiles<S, 1>(slots + (live > 2 ? 2 : 1) * SE, slots, team >> 1, team & 1, C, L);
+            P = C[0];
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const d2_t v = slots[P.row(L, team, r) * LD + P.col(L, team)];
+                P.re[r] = v.x;
+                P.im[r] = v.y;
+            }
+        }
+    }
+    return P;
+}
+
+// The ticketed product tree (fan-in kFanIn) of blocks of four one-wave teams,
+// which stay together into it: the block's node is published and team 0 takes its
+// group's ticket; in the group's last arrival team w multiplies nodes 2 w + 1 and
+// 2 w, read straight from memory, and mx_combine does the rest.
+template <class S>
+__device__ void mx_tree(const PropParams& p, int64_t leaf, Part<S> Q, int team, d2_t* slots, int* tick,
                         const WLane& L) {
     static_assert(2 * kWaveTeams == kFanIn && !S::kPair, "two nodes per team");
     constexpr int64_t NN = (int64_t)256 * S::NT * S::NT * 2;
+    const bool mine = Q.mine(team);
     int64_t idx = leaf, cnt = p.n_leaves, off = 0;
     while (cnt > 1) {
         const int64_t pcnt = (cnt + kFanIn - 1) / kFanIn, poff = off + cnt, grp = idx / kFanIn;
         const int64_t first = grp * kFanIn;
         const int members = (int)(min(cnt, first + kFanIn) - first);
         if (members == 1) {
-            if (p.store_nodes && team == 0) mx_node_store<S>(p.nodes + (off + idx) * NN, Q, L);
+            if (p.store_nodes && mine) part_store<S>(p.nodes + (off + idx) * NN, Q, team, L);
         } else {
+            if (mine) part_publish<S>(p.nodes + (off + idx) * NN, Q, team, L);
+            if constexpr (S::NT > 1) __syncthreads();   // every team's tile is out
             if (team == 0) {
-                mx_node_publish<S>(p.nodes + (off + idx) * NN, Q, L);
                 unsigned v = 0;
                 if (L.lane == 0) v = atomicAdd(&p.counters[poff + grp], 1u);
                 const unsigned t = (unsigned)__builtin_amdgcn_readfirstlane((int)v);
@@ -573,21 +681,22 @@ __device__ void mx_tree(const PropParams& p, int64_t leaf, Mx<S>& Q, int team, d
             __syncthreads();
             if (t != members - 1) return;   // the whole block leaves
             double* nd = p.nodes + (off + first + 2 * team) * NN;
+            Mx<S> M;
             if (2 * team + 1 < members) {
                 const Mx<S> A = mx_node_fetch<S, true>(nd + NN, L);
-                Q = mx_node_mul<S>(A, mx_node_fetch<S, false>(nd, L), L);
+                M = mx_node_mul<S>(A, mx_node_fetch<S, false>(nd, L), L);
             } else if (2 * team < members) {
-                Q = mx_node_fetch<S, false>(nd, L);
+                M = mx_node_fetch<S, false>(nd, L);
             }
-            mx_combine<S>(Q, team, (members + 1) / 2, slots, L);
+            Q = mx_combine<S>(M, team, (members + 1) / 2, slots, L);
         }
         idx = grp;
         off = poff;
         cnt = pcnt;
     }
-    if (team != 0) return;
-    if (p.store_nodes) mx_node_store<S>(p.nodes + off * NN, Q, L);
-    mx_store_root<S>(p, Q, L);
+    if (!mine) return;
+    if (p.store_nodes) part_store<S>(p.nodes + off * NN, Q, team, L);
+    part_store_root<S>(p, Q, team, L);
 }
 
 }  // namespace

@@ -123,8 +123,8 @@ __attribute__((amdgpu_waves_per_eu(S::NT == 1 ? 2 : 1, S::NT == 1 ? 8 : 1))) pro
     }
     // (mx_combine's first barrier comes after every team's last use of the
     // basis and the scratch tiles)
-    mx_combine<Node>(N, team, kWaveTeams, slots, L);
-    mx_tree<Node>(p, blockIdx.x, N, team, slots, tick, L);
+    const Part<Node> B = mx_combine<Node>(N, team, kWaveTeams, slots, L);
+    mx_tree<Node>(p, blockIdx.x, B, team, slots, tick, L);
 }
 
 // LDS of a launch: a ticket, then the run's part (with `aside` two matrices more
