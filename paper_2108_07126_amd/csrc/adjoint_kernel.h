@@ -396,15 +396,20 @@ hipError_t pick_wave16(const PropParams& p, const A& a, hipStream_t stream) {
                       : F::template run<Wide<1, 4>, EXPO_BASIS, true>(a, stream);
 }
 
+template <class F, int EXPO, class A>
+hipError_t pick_slices(const PropParams& p, const A& a, hipStream_t stream) {
+    if (p.du <= 24) return F::template run<Wide<2, 6>, EXPO, true>(a, stream);
+    return p.du <= 28 ? F::template run<Wide<2, 7>, EXPO, true>(a, stream)
+                      : F::template run<Wide<2, 8>, EXPO, true>(a, stream);
+}
+
 template <class F, class A>
 hipError_t pick_wave32(const PropParams& p, const A& a, hipStream_t stream) {
     if (adjoint_lds_bytes<2>(p.M, true) <= 160 * 1024 && p.M <= kWaveBasis)
-        return p.du <= 24 ? F::template run<Wide<2, 6>, EXPO_BASIS, true>(a, stream)
-                          : F::template run<Wide<2, 8>, EXPO_BASIS, true>(a, stream);
+        return pick_slices<F, EXPO_BASIS>(p, a, stream);
     if (p.order != 4) return F::template run<Wide<2, 8>, EXPO_BASIS, false>(a, stream);
     if (adjoint_lds_bytes<2>(p.K + 1, true) <= 160 * 1024)
-        return p.du <= 24 ? F::template run<Wide<2, 6>, EXPO_COMM, true>(a, stream)
-                          : F::template run<Wide<2, 8>, EXPO_COMM, true>(a, stream);
+        return pick_slices<F, EXPO_COMM>(p, a, stream);
     return F::template run<Wide<2, 8>, EXPO_COMM, false>(a, stream);
 }
 

@@ -7,7 +7,8 @@ namespace {
 template <int EXPO>
 hipError_t launch_k(const PropParams& p, int nb, hipStream_t stream) {
     if (wave_lds_bytes<2>(nb, true) > 160 * 1024) return launch_wave_one<Wide<2, 8>, EXPO, false, false>(p, stream);
-    return p.du <= 24 ? launch_wave_one<Wide<2, 6>, EXPO, false, true>(p, stream)
+    if (p.du <= 24) return launch_wave_one<Wide<2, 6>, EXPO, false, true>(p, stream);
+    return p.du <= 28 ? launch_wave_one<Wide<2, 7>, EXPO, false, true>(p, stream)
                       : launch_wave_one<Wide<2, 8>, EXPO, false, true>(p, stream);
 }
 

@@ -80,7 +80,14 @@ __attribute__((amdgpu_waves_per_eu(S::NT == 1 ? 2 : 1, S::NT == 1 ? 8 : 1))) pro
                             d2_t{E.re[e] + (ro == co ? 1.0 : 0.0), -E.im[e]};
                 });
         }
-        Q = mx_apply<S>(E, Q);
+        if (S::NT > 1 && t == 0) {
+            // (two tiles wide the first product, with the identity, is the length
+            // of a short chain's whole series: it is a transposition)
+            Q = mx_adjoint<S>(E, sl.scr, L);
+            mx_each<S>([&](int e) { Q.re[e] += mx_diag<S>(L, e) ? 1.0 : 0.0; });
+        } else {
+            Q = mx_apply<S>(E, Q);
+        }
     }
     Mx<Node> N;
     if constexpr (S::kPair) {
