@@ -411,12 +411,13 @@ __device__ __forceinline__ Strip<NT> strip_node_load_adj(const double* node, con
     return Q;
 }
 
-// A node less the identity: the tree joins nodes as X + (A - I) X, which rounds
+// Take the identity from a staged node (the wave that staged its diagonal entries
+// does, before the barrier): the tree joins nodes as X + (A - I) X, which rounds
 // relative to ||A - I|| (mx_join in mfma_wave.h).
 template <int NT>
-__device__ __forceinline__ Strip<NT> strip_less_one(Strip<NT> A, const SLane& L) {
-    strip_each<NT>([&](int k, int r) { A.t[k].re[r] -= strip_diag(L, k, r) ? 1.0 : 0.0; });
-    return A;
+__device__ __forceinline__ void strip_staged_less_one(char* slot, const SLane& L) {
+    double* s = reinterpret_cast<double*>(slot);
+    if (L.lane < 16) s[2 * strip_at<NT>(16 * L.c + L.lane, 16 * L.c + L.lane)] -= 1.0;
 }
 
 // Root product into U_out.
@@ -473,11 +474,12 @@ __device__ void strip_tree(const PropParams& p, int64_t leaf, Strip<NT> Q, const
                 char* s = sl.next();
                 if (active) {
                     if (idx == first) {
-                        strip_stage<NT>(s, strip_less_one<NT>(strip_node_load_adj<NT>(p.nodes + (off + first + 1) * NN, L), L), L);
+                        strip_stage<NT>(s, strip_node_load_adj<NT>(p.nodes + (off + first + 1) * NN, L), L);
                     } else {
-                        strip_stage_adj<NT>(s, strip_less_one<NT>(Q, L), L);
+                        strip_stage_adj<NT>(s, Q, L);
                         Q = strip_node_load<NT>(p.nodes + (off + first) * NN, L);
                     }
+                    strip_staged_less_one<NT>(s, L);
                 }
                 __syncthreads();
                 if (active) strip_add<NT>(Q, strip_mul<NT, KS>(s, Q, L));
@@ -485,8 +487,10 @@ __device__ void strip_tree(const PropParams& p, int64_t leaf, Strip<NT> Q, const
                 if (active) Q = strip_node_load<NT>(p.nodes + (off + first) * NN, L);
                 for (int64_t k = first + 1; k < first + members; ++k) {
                     char* s = sl.next();
-                    if (active)
-                        strip_stage<NT>(s, strip_less_one<NT>(strip_node_load_adj<NT>(p.nodes + (off + k) * NN, L), L), L);
+                    if (active) {
+                        strip_stage<NT>(s, strip_node_load_adj<NT>(p.nodes + (off + k) * NN, L), L);
+                        strip_staged_less_one<NT>(s, L);
+                    }
                     __syncthreads();
                     if (active) strip_add<NT>(Q, strip_mul<NT, KS>(s, Q, L));
                 }
