@@ -54,17 +54,18 @@ struct PropParams {
     double* chain_out;        // nullptr or [n_chains][D][D] complex128 chain products
     int store_nodes;          // keep every tree node (gradient checkpoints)
     double h;
-    double theta[kMaxDeg + 1];   // Taylor thresholds for the working precision
-    double sth[kSchemes];        // largest ||G||_2 for scheme q (-1: past the degree cap)
-    int qmax;                    // the last available scheme
-    double tc[scheme_degree(kSchemes - 1) + 1];   // 1/k!, zero past the degree cap
-    double beta[kMaxBasis];      // upper bounds of ||B_m||_2
     int K, M, order, du;
     int max_degree, force_s;
     int basis_lds;               // MFMA engine: block keeps a copy of the basis in LDS
     int pair;                    // MFMA engines, D = 16: two slices of dimension <= 8 per tile
     int method;                  // PM_EXPM_TAYLOR or PM_EXPM_CHEBYSHEV
+    int qmax;                    // the last available scheme
     const double* cheb_j;        // Chebyshev: [m][k] = J_k(ctheta[m]), k <= m <= kMaxCheb; then the split rows
+    // (tables behind what every kernel reads first)
+    double sth[kSchemes];        // largest ||G||_2 for scheme q (-1: past the degree cap)
+    double beta[kMaxBasis];      // upper bounds of ||B_m||_2
+    double tc[scheme_degree(kSchemes - 1) + 1];   // 1/k!, zero past the degree cap
+    double theta[kMaxDeg + 1];   // Taylor thresholds for the working precision
     double ctheta[kMaxCheb + 1]; // Chebyshev: half-width of the spectral interval for degree m
     uint8_t pair_a[kMaxBasis];   // order 4: control indices of i[H_a, H_b]
     uint8_t pair_b[kMaxBasis];
