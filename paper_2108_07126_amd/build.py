@@ -14,8 +14,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libparament.so")
-SOURCES = ["parament.cpp", "engine_mfma.hip", "engine_mfma_pair.hip", "engine_wave.hip", "engine_wave_32.hip", "engine_wave_alt.hip", "engine_strip.hip", "engine_panel.hip", "engine_valu.hip", "engine_valu_f64_2.hip", "engine_valu_f64_4.hip",
-           "engine_valu_f32_2.hip", "engine_valu_f32_4.hip", "engine_grad.hip", "engine_adjoint_16.hip", "engine_adjoint_32.hip", "engine_trajectory_16.hip", "engine_trajectory_32.hip", "engine_batch.hip", "engine_grape.hip", "noalloc.hip"]
+SOURCES = ["parament.cpp", "norm_bound.cpp", "engine_mfma.hip", "engine_mfma_pair.hip", "engine_wave.hip", "engine_wave_32.hip", "engine_wave_alt.hip", "engine_strip.hip", "engine_panel.hip", "engine_valu.hip", "engine_valu_f64_2.hip", "engine_valu_f64_4.hip",
+           "engine_valu_f32_2.hip", "engine_valu_f32_4.hip", "engine_grad.hip", "engine_adjoint_16.hip", "engine_adjoint_32.hip", "engine_trajectory_16.hip", "engine_trajectory_32.hip", "engine_batch.hip", "engine_grape.hip", "engine_bounds.hip", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

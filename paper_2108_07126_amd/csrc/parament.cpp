@@ -22,6 +22,8 @@ hipError_t launch_backward(int D, const GradParams& gp, double* grad_samples, hi
 hipError_t launch_batch(int precision, const BatchParams& bp, int blocks, hipStream_t stream, hipStream_t side,
                         hipEvent_t fork, hipEvent_t join);
 hipError_t batch_setup(int precision);
+double norm2_bound(const std::complex<double>* a, int d, double n1);
+hipError_t launch_norm2_bounds(int D, const double* basis, double* bounds, int n, hipStream_t stream);
 }  // namespace pm
 
 using cplx = std::complex<double>;
@@ -38,7 +40,6 @@ struct pm_ctx {
     pm::EngineInfo eng{};
     std::vector<double> basis;   // FP64 [M][dim][dim] interleaved
     std::vector<double> norms;   // [M]
-    std::vector<double> beta;    // [M] bounds of the 2-norms (tile engines)
     uint8_t pair_a[pm::kMaxBasis] = {};
     uint8_t pair_b[pm::kMaxBasis] = {};
     double theta[pm::kMaxDeg + 1] = {};
@@ -347,55 +348,6 @@ double norm1(const Mat& a, int64_t d) {
         best = std::max(best, s);
     }
     return best;
-}
-
-// Upper bound of ||A||_2 of a Hermitian A: (||A^n||_F)^(1/n), n = 16 (8 past 32
-// levels) by repeated squaring of the scaled matrix, never above ||A||_1.  It
-// is within d^(1/2n) of the 2-norm (9 % at d = 16, 30 % at d = 64, a third of
-// that for a GUE matrix).  Real and imaginary planes, so the inner loop is a
-// plain vector update.
-double norm2_bound(const Mat& a, int64_t d) {
-    const double n1 = norm1(a, d);
-    if (!(n1 > 0.0)) return 0.0;
-    const int squarings = d <= 32 ? 4 : 3;
-    std::vector<double> xr((size_t)(d * d)), xi(xr.size()), yr(xr.size()), yi(xr.size());
-    for (int64_t i = 0; i < d * d; ++i) {
-        xr[i] = a[i].real() / n1;
-        xi[i] = a[i].imag() / n1;
-    }
-    double lg = 0.0;   // log ||A^n / n1^n||_F
-    for (int k = 0; k < squarings; ++k) {
-        // the upper triangle: every power is Hermitian
-        double f = 0.0;
-        for (int64_t i = 0; i < d; ++i) {
-            double *rr = &yr[i * d], *ri = &yi[i * d];
-            std::fill(rr + i, rr + d, 0.0);
-            std::fill(ri + i, ri + d, 0.0);
-            for (int64_t q = 0; q < d; ++q) {
-                const double ar = xr[i * d + q], ai = xi[i * d + q];
-                const double *br = &xr[q * d], *bi = &xi[q * d];
-                for (int64_t j = i; j < d; ++j) {
-                    rr[j] += ar * br[j] - ai * bi[j];
-                    ri[j] += ar * bi[j] + ai * br[j];
-                }
-            }
-            for (int64_t j = i; j < d; ++j) {
-                f += (j > i ? 2.0 : 1.0) * (rr[j] * rr[j] + ri[j] * ri[j]);
-                yr[j * d + i] = rr[j];
-                yi[j * d + i] = -ri[j];
-            }
-            ri[i] = 0.0;
-        }
-        f = std::sqrt(f);
-        if (!(f > 0.0)) return n1 * (1.0 + 1e-6);
-        lg = 2.0 * lg + std::log(f);
-        const double inv = 1.0 / f;
-        for (int64_t i = 0; i < d * d; ++i) {
-            xr[i] = yr[i] * inv;
-            xi[i] = yi[i] * inv;
-        }
-    }
-    return std::min(n1, n1 * std::exp(lg / (1 << squarings))) * (1.0 + 1e-6);
 }
 
 // The ordered basis: H0, H_1..H_K [, i[H0,H_k] (k=1..K), i[H_k,H_k'] (k<k')].
@@ -817,7 +769,7 @@ pm_status prepare(pm_ctx* ctx, const pm::EngineInfo& e, bool keep_nodes, const d
         std::memcpy(p.sth, ctx->schemes.sth, sizeof(p.sth));
         std::memcpy(p.tc, ctx->schemes.tc, sizeof(p.tc));
         p.qmax = ctx->schemes.qmax;
-        for (int m = 0; m < ctx->M; ++m) p.beta[m] = ctx->beta[m];
+        p.beta = basis + pm::basis_layout_doubles(e, ctx->M);
     }
     p.K = (int)ctx->n_ctrl;
     p.M = ctx->M;
@@ -1324,8 +1276,19 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
         }
         norms[m] = norm1(basis[m], dim);
     }
-    std::vector<double> lay((size_t)pm::basis_layout_doubles(e, M));
-    pm::basis_to_layout(e, M, (int)dim, flat.data(), lay.data());
+    // The FP64 tile engines read bounds of the matrices' 2-norms behind the basis.
+    // (The commutators' weights are small: their 1-norm serves; the reduced
+    // precisions plan by the exponent's 1-norm.  Past 16 levels the 1-norms of the
+    // others are replaced on the device.)
+    auto layout = [&](const pm::EngineInfo& en, bool bounds) {
+        const size_t n = (size_t)pm::basis_layout_doubles(en, M);
+        std::vector<double> to(n + (bounds ? M : 0));
+        pm::basis_to_layout(en, M, (int)dim, flat.data(), to.data());
+        for (int m = 0; bounds && m < M; ++m)
+            to[n + m] = m <= n_ctrl && dim <= 16 ? pm::norm2_bound(basis[m].data(), (int)dim, norms[m]) : norms[m] * (1.0 + 1e-6);
+        return to;
+    };
+    const std::vector<double> lay = layout(e, ctx->precision == PM_FP64 && e.kind == pm::ENGINE_MFMA);
 
     DeviceGuard g(ctx->device);
     if (!g.ok) return hip_fail(ctx, hipErrorInvalidDevice, "hipSetDevice");
@@ -1349,8 +1312,7 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
         pm::pick_engine(dim <= 16 ? 16 : (int)dim, PM_FP64, &ge);
         ctx->geng = ge;
         if (e.kind != pm::ENGINE_MFMA) {
-            std::vector<double> glay((size_t)pm::basis_layout_doubles(ge, M));
-            pm::basis_to_layout(ge, M, (int)dim, flat.data(), glay.data());
+            const std::vector<double> glay = layout(ge, true);
             he = hipMalloc((void**)&ctx->d_basis_grad, glay.size() * sizeof(double));
             if (he != hipSuccess) {
                 ctx->d_basis_grad = nullptr;
@@ -1360,6 +1322,12 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
             }
             he = hipMemcpy(ctx->d_basis_grad, glay.data(), glay.size() * sizeof(double), hipMemcpyHostToDevice);
             if (he != hipSuccess) return hip_fail(ctx, he, "hipMemcpy gradient basis");
+        }
+        if (dim > 16) {
+            he = pm::launch_norm2_bounds(e.D, ctx->d_basis, ctx->d_basis + pm::basis_layout_doubles(e, M),
+                                         (int)n_ctrl + 1, nullptr);
+            if (he == hipSuccess) he = hipStreamSynchronize(nullptr);
+            if (he != hipSuccess) return hip_fail(ctx, he, "bounds of the basis");
         }
     }
     // slice pairs of the reduced precisions: the basis in both diagonal 8 x 8
@@ -1394,12 +1362,6 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
     ctx->eng = e;
     ctx->basis = flat;
     ctx->norms = norms;
-    ctx->beta.resize(M);
-    // (the commutators' weights are small: their 1-norm serves; the reduced
-    // precisions plan by the exponent's 1-norm)
-    for (int m = 0; m < M; ++m)
-        ctx->beta[m] = m <= n_ctrl && ctx->precision == PM_FP64 ? norm2_bound(basis[m], dim)
-                                                                : norms[m] * (1.0 + 1e-6);
     std::memset(ctx->pair_a, 0, sizeof(ctx->pair_a));
     std::memset(ctx->pair_b, 0, sizeof(ctx->pair_b));
     for (size_t q = 0; q < pairs.size(); ++q) {

@@ -38,6 +38,7 @@ constexpr int kWaveBasis = 16;
 // argument.  Pointers are device pointers.
 struct PropParams {
     const double* basis;      // Hermitian basis in the engine's layout, FP64
+    const double* beta;       // FP64 tile engines: upper bounds of ||B_m||_2
     const double* samples;    // [K][n_samples]
     int64_t n_samples;
     int64_t n_slices;         // N
@@ -63,7 +64,6 @@ struct PropParams {
     const double* cheb_j;        // Chebyshev: [m][k] = J_k(ctheta[m]), k <= m <= kMaxCheb; then the split rows
     // (tables behind what every kernel reads first)
     double sth[kSchemes];        // largest ||G||_2 for scheme q (-1: past the degree cap)
-    double beta[kMaxBasis];      // upper bounds of ||B_m||_2
     double tc[scheme_degree(kSchemes - 1) + 1];   // 1/k!, zero past the degree cap
     double theta[kMaxDeg + 1];   // Taylor thresholds for the working precision
     double ctheta[kMaxCheb + 1]; // Chebyshev: half-width of the spectral interval for degree m

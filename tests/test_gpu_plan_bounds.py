@@ -74,3 +74,36 @@ def test_units(pm, d, K, e):
         assert orc.relative_frobenius(out[1][0], Uo) <= 1e-10, order
         for a, b in zip(*out):
             assert np.array_equal(a, b), order
+
+
+@pytest.mark.parametrize("d", [3, 5, 8, 11, 16, 17, 24, 32, 33, 64])
+@pytest.mark.parametrize("kind", ["zero", "diagonal", "rank one", "one pair", "identity"])
+def test_norms_of_special_matrices(pm, d, kind):
+    """Norms whose bound has nothing to spare (a single eigenvalue, all alike) and a
+    basis of zeros: from a short to a long series the slices keep FP64 accuracy
+    (64 sqrt(n d) 2^-53, doubled by each squaring), gradients included."""
+    import torch
+    rng = np.random.default_rng(d)
+    v = rng.standard_normal((d, 1)) + 1j * rng.standard_normal((d, 1))
+    v /= np.linalg.norm(v)
+    A = {"zero": np.zeros((d, d)), "diagonal": np.diag(np.linspace(-1.0, 0.9, d)), "rank one": v @ v.conj().T,
+         "one pair": np.zeros((d, d), complex), "identity": np.eye(d)}[kind].astype(complex)
+    if kind == "one pair":
+        A[0, d - 1], A[d - 1, 0] = 1j, -1j
+    w = synth.random_system(d, 1, n_slices=7, h=0.1, order=2, tag=1140)
+    for H0, Hk in ((A, w.Hk), (w.H0, A[None]), (A, A[None])):
+        for h in (1e-6, 0.05, 0.4, 3.0):
+            print(f"[case] {kind} d={d} h={h}", file=sys.stderr, flush=True)
+            V = rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d))
+            with pm.Context(0, pm.PM_FP64) as ctx:
+                ctx.set_hamiltonian(H0, Hk, 2)
+                U = ctx.equiprop(w.samples, h)
+                c = torch.from_numpy(w.samples).cuda()
+                g = torch.zeros_like(c)
+                ctx.backward_dev(c, h, torch.from_numpy(V).cuda(), g)
+                torch.cuda.synchronize()
+            Uo = orc.propagate(H0, Hk, w.samples, h, 2)
+            _, go = orc.control_gradient(H0, Hk, w.samples, h, 2, V)
+            tol = 64 * np.sqrt(7 * d) * 2.0 ** -53 * max(1.0, 4 * h)
+            assert orc.relative_frobenius(U, Uo) <= tol
+            assert np.max(np.abs(g.cpu().numpy() - go)) <= 4 * tol * h * np.linalg.norm(V) * max(1.0, np.linalg.norm(Hk[0], 2))
