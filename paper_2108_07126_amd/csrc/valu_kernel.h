@@ -328,10 +328,6 @@ __device__ __forceinline__ Mat<D, T> exp_ch(Herm<D, T> x, int m, const double* j
             const int e = hidx<D>(a, b);
             double ar = cre[1] * x.re[e], ai = cre[1] * x.im[e];
             double br = cim[1] * x.re[e], bi = cim[1] * x.im[e];
-            if (a == b) {
-                ar += cre[0];
-                br += cim[0];
-            }
             if constexpr (D == 4) {
                 // (X^3)_{ab} = sum_k X_{ak} (X^2)_{kb}
                 double tr = 0.0, ti = 0.0;
@@ -347,8 +343,10 @@ __device__ __forceinline__ Mat<D, T> exp_ch(Herm<D, T> x, int m, const double* j
                 br = fma(cim[2], x2.re[e], fma(cim[3], tr, br));
                 bi = fma(cim[2], x2.im[e], fma(cim[3], ti, bi));
             }
-            U.re[a * D + b] = (T)(ar - bi);
-            U.im[a * D + b] = (T)(ai + br);
+            // c_0 I last: every other sum is of ||X||'s size, so the diagonal
+            // rounds at the size of one only once
+            U.re[a * D + b] = (T)(a == b ? cre[0] + (ar - bi) : ar - bi);
+            U.im[a * D + b] = (T)(a == b ? cim[0] + (ai + br) : ai + br);
             if (a != b) {
                 U.re[b * D + a] = (T)(ar + bi);
                 U.im[b * D + a] = (T)(br - ai);
