@@ -157,7 +157,7 @@ __device__ void run_panel_packet(const PropParams& p, const BatchPacket& P, char
     const Strip<4> X = panel_to_strips(Q, lds, L);
     const SLane S{L.lane, L.g, L.j, L.w};
     Slots sl{{lds, lds + strip_slot_bytes<4>()}, 0};
-    strip_tree<4, 4 * RT>(p, P.leaf, X, S, sl, reinterpret_cast<int*>(lds + kPanelLds - 16), L.team == 0);
+    strip_tree<4, 4 * RT, false>(p, P.leaf, X, S, sl, reinterpret_cast<int*>(lds + kPanelLds - 16), L.team == 0);
 }
 
 template <int PMODE>

@@ -20,9 +20,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (p.chain_out && chain < p.n_chains) strip_node_store<4>(p.chain_out + chain * (int64_t)kPanelD * kPanelD * 2, X, S);
     Slots sl{{lds, lds + strip_slot_bytes<4>()}, 0};
     int* tick = reinterpret_cast<int*>(lds + kPanelLds - 16);
-    if constexpr (RT == 4) strip_tree<4, 16>(p, blockIdx.x, X, S, sl, tick);
-    else if (p.du > 40) strip_tree<4, 12>(p, blockIdx.x, X, S, sl, tick);
-    else strip_tree<4, 10>(p, blockIdx.x, X, S, sl, tick);
+    if constexpr (RT == 4) strip_tree<4, 16, false>(p, blockIdx.x, X, S, sl, tick);
+    else if (p.du > 40) strip_tree<4, 12, false>(p, blockIdx.x, X, S, sl, tick);
+    else strip_tree<4, 10, false>(p, blockIdx.x, X, S, sl, tick);
 }
 
 template <int PMODE, int RT, bool OUT>

@@ -211,7 +211,7 @@ propagate_strip(PropParams p) {
         }
     }
     if (p.chain_out && chain < p.n_chains) strip_node_store<NT>(p.chain_out + chain * (int64_t)D * D * 2, Q, L);
-    strip_tree<NT, KS>(p, blockIdx.x, Q, L, sl, tick);
+    strip_tree<NT, KS, true>(p, blockIdx.x, Q, L, sl, tick);
 }
 
 template <int D, int KS, bool CH, bool M6>

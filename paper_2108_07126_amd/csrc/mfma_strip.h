@@ -420,6 +420,13 @@ __device__ __forceinline__ void strip_staged_less_one(char* slot, const SLane& L
     if (L.lane < 16) s[2 * strip_at<NT>(16 * L.c + L.lane, 16 * L.c + L.lane)] -= 1.0;
 }
 
+template <int NT, int KS, bool JOIN>
+__device__ __forceinline__ Strip<NT> strip_node_mul(const char* s, const Strip<NT>& X, const SLane& L) {
+    Strip<NT> y = strip_mul<NT, KS>(s, X, L);
+    if constexpr (JOIN) strip_add<NT>(y, X);
+    return y;
+}
+
 // Root product into U_out.
 template <int NT>
 __device__ __forceinline__ void strip_store_root(const PropParams& p, const Strip<NT>& Q, const SLane& L) {
@@ -443,7 +450,10 @@ __device__ __forceinline__ void strip_store_root(const PropParams& p, const Stri
 // kFanIn nodes that the checkpoints are assembled from, multiplied the earliest
 // first, each left factor's adjoint read straight from memory.  Waves past the
 // strips (active false) only keep the barriers.
-template <int NT, int KS>
+// JOIN: nodes are joined as X + (A - I) X.  (The reduced precisions' chains round a
+// million times more, and their two waves per SIMD have no registers for X beside
+// the product: 65536 slices of 64 levels in BF16 split 2854 us, with JOIN 2961.)
+template <int NT, int KS, bool JOIN>
 __device__ void strip_tree(const PropParams& p, int64_t leaf, Strip<NT> Q, const SLane& L, Slots& sl, int* tick,
                            bool active = true) {
     constexpr int64_t NN = (int64_t)256 * NT * NT * 2;
@@ -479,20 +489,20 @@ __device__ void strip_tree(const PropParams& p, int64_t leaf, Strip<NT> Q, const
                         strip_stage_adj<NT>(s, Q, L);
                         Q = strip_node_load<NT>(p.nodes + (off + first) * NN, L);
                     }
-                    strip_staged_less_one<NT>(s, L);
+                    if constexpr (JOIN) strip_staged_less_one<NT>(s, L);
                 }
                 __syncthreads();
-                if (active) strip_add<NT>(Q, strip_mul<NT, KS>(s, Q, L));
+                if (active) Q = strip_node_mul<NT, KS, JOIN>(s, Q, L);
             } else {
                 if (active) Q = strip_node_load<NT>(p.nodes + (off + first) * NN, L);
                 for (int64_t k = first + 1; k < first + members; ++k) {
                     char* s = sl.next();
                     if (active) {
                         strip_stage<NT>(s, strip_node_load_adj<NT>(p.nodes + (off + k) * NN, L), L);
-                        strip_staged_less_one<NT>(s, L);
+                        if constexpr (JOIN) strip_staged_less_one<NT>(s, L);
                     }
                     __syncthreads();
-                    if (active) strip_add<NT>(Q, strip_mul<NT, KS>(s, Q, L));
+                    if (active) Q = strip_node_mul<NT, KS, JOIN>(s, Q, L);
                 }
             }
         }
