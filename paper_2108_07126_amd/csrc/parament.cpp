@@ -145,11 +145,11 @@ double taylor_theta(int m, double u, bool relative) {
         return relative ? (th > 0.0 ? t / th : 0.0) : t;
     };
     double lo = 0.0, hi = m + 1.0;   // bound is increasing on [0, m+2)
-    for (int it = 0; it < 200; ++it) {
+    for (;;) {
         const double mid = 0.5 * (lo + hi);
+        if (!(lo < mid && mid < hi)) return lo;   // neighbours
         if (bound(mid) <= u) lo = mid; else hi = mid;
     }
-    return lo;
 }
 
 int taylor_products_host(int m) {
