@@ -1,6 +1,6 @@
-// Propagation on strip teams (mfma_strip.h): FP64, dimensions 17..64.
+// Propagation on strip teams (mfma_strip.h): FP64, dimensions 33..64.
 //
-// A block is one team of D/16 waves running a chain of consecutive slices.
+// A block is one team of four waves running a chain of consecutive slices.
 // Per slice: the bound sum |w_m| ||B_m||_2 of the lanes' weights picks the
 // series' scheme; E = exp(i G) - I; optionally the slice exp(-i G) = I + E^H
 // is stored; Q <- Q + E^H Q.  The next slice's exponent is expanded while the
@@ -67,11 +67,12 @@ struct Expand {
     }
 };
 
-// Waves per SIMD: at D = 64 three operands of the series, the chain product
-// and the accumulators (64 registers a strip) take one wave's 512 registers.
-template <int D, int KS, bool CH, bool M6>
-__global__ void __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(D == 64 ? 1 : 2, D == 64 ? 1 : 2)))
-propagate_strip(PropParams p) {
+constexpr int D = 64;
+
+// One wave per SIMD: three operands of the series, the chain product and the
+// accumulators (64 registers a strip) take a wave's 512 registers.
+template <int KS, bool CH, bool M6>
+__global__ void __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(1, 1))) propagate_strip(PropParams p) {
     constexpr int NT = D / 16;
     constexpr int RT = (KS + 3) / 4;
     constexpr size_t SB = strip_slot_bytes<NT>();
@@ -214,44 +215,40 @@ propagate_strip(PropParams p) {
     strip_tree<NT, KS, true>(p, blockIdx.x, Q, L, sl, tick);
 }
 
-template <int D, int KS, bool CH, bool M6>
+template <int KS, bool CH, bool M6>
 hipError_t launch_strip_one(const PropParams& p, hipStream_t stream) {
     constexpr size_t lds = 2 * strip_slot_bytes<D / 16>() + 64;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)propagate_strip<D, KS, CH, M6>,
+        hipError_t e = hipFuncSetAttribute((const void*)propagate_strip<KS, CH, M6>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((propagate_strip<D, KS, CH, M6>), dim3((unsigned)p.n_leaves), dim3(4 * D), lds, stream, p);
+    hipLaunchKernelGGL((propagate_strip<KS, CH, M6>), dim3((unsigned)p.n_leaves), dim3(4 * D), lds, stream, p);
     return hipGetLastError();
 }
 
 // The Taylor series of orders 2, 4 and CF4 over the k-slices the dimension
-// reaches, in steps of two; the Chebyshev series over three quarters or all of
-// them, the sixth-order scheme over all.
-template <int D, int KS>
+// reaches, in steps of two.
+template <int KS>
 hipError_t launch_strip_ks(const PropParams& p, hipStream_t stream) {
     if constexpr (KS < D / 4) {
-        if (p.du > 4 * KS) return launch_strip_ks<D, KS + 2>(p, stream);
+        if (p.du > 4 * KS) return launch_strip_ks<KS + 2>(p, stream);
     }
-    return launch_strip_one<D, KS, false, false>(p, stream);
-}
-
-template <int D>
-hipError_t launch_strip_d(const PropParams& p, hipStream_t stream) {
-    const bool ch = p.method == PM_EXPM_CHEBYSHEV;
-    if (p.order == kOrderM6)
-        return ch ? launch_strip_one<D, D / 4, true, true>(p, stream) : launch_strip_one<D, D / 4, false, true>(p, stream);
-    if (ch)
-        return p.du <= 3 * D / 4 ? launch_strip_one<D, 3 * D / 16, true, false>(p, stream)
-                                 : launch_strip_one<D, D / 4, true, false>(p, stream);
-    return launch_strip_ks<D, D / 8 + 2>(p, stream);
+    return launch_strip_one<KS, false, false>(p, stream);
 }
 
 }  // namespace
 
-hipError_t launch_strip(const PropParams& p, hipStream_t stream) { return launch_strip_d<64>(p, stream); }
+// (The Chebyshev series runs over three quarters or all of the k-slices, the
+// sixth-order scheme over all.)
+hipError_t launch_strip(const PropParams& p, hipStream_t stream) {
+    const bool ch = p.method == PM_EXPM_CHEBYSHEV;
+    if (p.order == kOrderM6)
+        return ch ? launch_strip_one<16, true, true>(p, stream) : launch_strip_one<16, false, true>(p, stream);
+    if (ch) return p.du <= 48 ? launch_strip_one<12, true, false>(p, stream) : launch_strip_one<16, true, false>(p, stream);
+    return launch_strip_ks<10>(p, stream);
+}
 
 }  // namespace pm

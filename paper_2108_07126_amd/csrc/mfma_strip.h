@@ -1,4 +1,5 @@
-// Strip teams: the FP64 MFMA engine of dimensions 17..64.
+// Strip teams: the FP64 MFMA engine of dimensions 33..64 (D = 64; the bounds of
+// engine_bounds.hip take D = 32 too).
 //
 // A team of NT = D/16 waves carries a chain; wave c owns the D x 16 column
 // strip [16 c, 16 c + 16) of every D x D complex matrix, NT tiles of 16 x 16 in

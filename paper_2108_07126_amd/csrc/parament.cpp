@@ -203,22 +203,18 @@ void fill_theta(double* theta, int precision, int64_t n) {
     for (int m = 1; m <= pm::kMaxDeg; ++m) theta[m] = taylor_theta(m, u, relative_truncation(precision));
 }
 
-// The tile engines' series: scheme q's threshold is the largest ||G||_2 whose
+// The FP64 tile engines' series: scheme q's threshold is the largest ||G||_2 whose
 // remainder stays below the rounding of the whole propagation.  The bound that
 // is compared with it is close to the 2-norm (a 1-norm is several times it),
-// so the target keeps an eighth of u / sqrt(N): truncation errors of
-// neighbouring slices add coherently, rounding errors like sqrt(N).  Reduced
-// precisions: relative to ||G||, and no scheme past degree 12 (||G|| ~ 1),
-// where terms grow well past the result.
-void fill_schemes(pm::PropParams& p, int precision, int64_t n, int max_degree) {
+// so the target keeps an eighth of u / sqrt(N), down to 2^-60: truncation errors
+// of neighbouring slices add coherently, rounding errors like sqrt(N).
+void fill_schemes(pm::PropParams& p, int64_t n, int max_degree) {
     const double u = std::max(std::ldexp(1.0, -60),
-                              unit_roundoff(precision) / (8.0 * std::sqrt((double)std::max<int64_t>(n, 1))));
+                              unit_roundoff(PM_FP64) / (8.0 * std::sqrt((double)std::max<int64_t>(n, 1))));
     p.qmax = 0;
     for (int q = 0; q < pm::kSchemes; ++q) {
-        const bool in = (q == 0 || pm::scheme_degree(q - 1) < max_degree) &&
-                        (precision == PM_FP64 || pm::scheme_degree(q) <= 12);
-        p.sth[q] = in ? taylor_theta(std::min(pm::scheme_degree(q), max_degree), u, relative_truncation(precision))
-                      : -1.0;
+        const bool in = q == 0 || pm::scheme_degree(q - 1) < max_degree;
+        p.sth[q] = in ? taylor_theta(std::min(pm::scheme_degree(q), max_degree), u, false) : -1.0;
         if (in) p.qmax = q;
     }
     double f = 1.0;
@@ -531,8 +527,9 @@ int64_t auto_chunk(const pm::EngineInfo& e, int64_t N, int precision, bool per_s
     // us, of 8 53.9 us, of 2 75.1 us; N = 4096 gradient, chains of 4 beat 2
     // by 13 % and 8 by 30 %.  Above 16 levels in FP64 a slice takes one wave (one
     // CU above 32) 10 us and more, a level of the tree as much: there a chain
-    // per SIMD (CU) comes first (27 levels: 1000 slices of a gradient 348 -> 187 us,
-    // 3000 fourth-order slices 142 -> 121 us; 64 levels, 600 slices 284 -> 244 us).
+    // per SIMD (CU) comes first (27 levels: 1000 slices of a gradient in chains of 4
+    // 254 us, of 1 139 us, 3000 fourth-order slices in chains of 4 103 us, of 3 89 us;
+    // 64 levels, 600 slices 254 and 224 us).
     const int64_t cmin = precision == PM_FP64 && e.D > 16 ? 1 : 4;
     if (e.kind == pm::ENGINE_MFMA && c < cmin) c = cmin;
     const int64_t u = e.chunk_unit;
@@ -760,9 +757,9 @@ pm_status prepare(pm_ctx* ctx, const pm::EngineInfo& e, bool keep_nodes, const d
         ctx->theta_n = N;
     }
     std::memcpy(p.theta, ctx->theta, sizeof(p.theta));
-    if (e.kind == pm::ENGINE_MFMA) {
+    if (e.kind == pm::ENGINE_MFMA && ctx->precision == PM_FP64) {
         if (ctx->scheme_n != N || ctx->scheme_cap != ctx->max_degree) {
-            fill_schemes(ctx->schemes, ctx->precision, N, ctx->max_degree);
+            fill_schemes(ctx->schemes, N, ctx->max_degree);
             ctx->scheme_n = N;
             ctx->scheme_cap = ctx->max_degree;
         }
