@@ -1,7 +1,7 @@
 // Bounds of the basis matrices' 2-norms above 16 levels (FP64 contexts), formed
-// where the basis already is: on the host three products of 64 levels take 150 us a
-// matrix, here 44 us for all of them with launch and wait, and 32 levels 30 us a
-// matrix against 24.  (Up to 16 levels the host's 4 us a matrix are less.)
+// where the basis already is.  On the host a matrix of 64 levels takes 150 us and
+// one of 32 levels 30 us; here all of them take 41 and 24 us with launch and wait.
+// (Up to 16 levels the host's 3 us a matrix are less: norm_bound.cpp.)
 #include "mfma_strip.h"
 
 namespace pm {

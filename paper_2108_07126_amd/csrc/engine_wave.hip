@@ -13,7 +13,9 @@ namespace {
 hipError_t launch_wave16(const PropParams& p, hipStream_t stream) {
     if (p.pair) return launch_wave_one<Pair<2>, EXPO_BASIS, false, true>(p, stream);
     // past that only fourth order with five controls or more (21 matrices):
-    // one commutator by product instead of K (K + 1) / 2 more basis matrices
+    // one commutator by product instead of K (K + 1) / 2 more basis matrices (8
+    // levels, 20000 slices, five controls: 52 us, in pairs on 21 matrices 77; eight
+    // controls: 60 us, one slice at a time on 45 matrices 247)
     if (p.M > kWaveBasis)
         return p.du <= 8 ? launch_wave_one<Wide<1, 2>, EXPO_COMM, false, true>(p, stream)
                          : launch_wave_one<Wide<1, 4>, EXPO_COMM, false, true>(p, stream);
