@@ -179,21 +179,12 @@ __device__ __forceinline__ Mx<S> mx_apply(const Mx<S>& A, const Mx<S>& X) {
 // A^H X of unitary A (a chain's or a node's adjoint) as X + (A - I)^H X: the
 // product rounds relative to ||A - I||, which is small where chains are short and
 // the tree takes over their products (a full product rounds ten times as much).
-// 27 levels, 278 slices: gradient 1.1e-14 -> 4.0e-15, U(T) 8.0e-15 -> 1.5e-15.
+// 27 levels, 278 slices: gradient 1.1e-14 -> 4.0e-15, U(T) 8.0e-15 -> 1.5e-15; 8 levels,
+// 1000 slices of a trajectory 6.2e-15 -> 2.5e-15 (16 levels, 1000 slices 22.1 -> 22.3 us).
 template <class S>
 __device__ __forceinline__ Mx<S> mx_join(Mx<S> A, const Mx<S>& X, const WLane& L) {
     mx_each<S>([&](int e) { A.re[e] -= mx_diag<S>(L, e) ? 1.0 : 0.0; });
     return mx_apply<S>(A, X);
-}
-
-// The tree's product.  Chains of one tile hold at least four slices, and few of
-// their products are the tree's: there the full product rounds no worse than the
-// chains and keeps short propagations a little shorter (16 levels, 1000 slices 22.1
-// against 22.3 us).
-template <class S>
-__device__ __forceinline__ Mx<S> mx_node_mul(const Mx<S>& A, const Mx<S>& X, const WLane& L) {
-    if constexpr (S::NT > 1) return mx_join<S>(A, X, L);
-    else return mx_mul<S>(A, X);
 }
 
 // exp(i G) - I for the (pre-scaled) Hermitian G by evaluation scheme q
@@ -607,7 +598,7 @@ __device__ __forceinline__ Part<S> mx_combine(Mx<S>& Q, int team, int live, d2_t
                     A.re[e] = v.x;
                     A.im[e] = -v.y;
                 });
-                Q = mx_mul<S>(A, Q);
+                Q = mx_join<S>(A, Q, L);
             }
         }
 #pragma unroll
@@ -684,7 +675,7 @@ __device__ void mx_tree(const PropParams& p, int64_t leaf, Part<S> Q, int team, 
             Mx<S> M;
             if (2 * team + 1 < members) {
                 const Mx<S> A = mx_node_fetch<S, true>(nd + NN, L);
-                M = mx_node_mul<S>(A, mx_node_fetch<S, false>(nd, L), L);
+                M = mx_join<S>(A, mx_node_fetch<S, false>(nd, L), L);
             } else if (2 * team < members) {
                 M = mx_node_fetch<S, false>(nd, L);
             }

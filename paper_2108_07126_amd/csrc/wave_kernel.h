@@ -108,7 +108,7 @@ __attribute__((amdgpu_waves_per_eu(S::NT == 1 ? 2 : 1, S::NT == 1 ? 8 : 1))) pro
             N.re[e] = in ? x.x : id;
             N.im[e] = in ? x.y : 0.0;
         });
-        N = mx_mul<Node>(A, N);
+        N = mx_join<Node>(A, N, L);
     } else {
         N = Q;
     }
