@@ -60,13 +60,50 @@ def taylor_products(m: int) -> int:
     return 0 if m <= 1 else (1 if m == 2 else m // 2 + 1)
 
 
-def series_products(m: int, precision: int, d: int) -> int:
-    """Products of the degree-m series: the FP64 tile engines (d > 4) evaluate
-    it in blocks of three powers, degree 1, 2, 4, 6, 9, 12, 15 in 0..6 products;
-    the others by the cos / sin split."""
-    if precision == 0 and d > 4:
-        return next((q for q, deg in enumerate((1, 2, 4, 6, 9, 12, 15)) if deg >= m), 6)
-    return taylor_products(m)
+# Degrees of the FP64 tile engines' series (blocks of three powers) in 0, 1, .. products.
+SCHEME_DEGREES = (1, 2, 4, 6, 9, 12, 15, 18, 21)
+
+
+def scheme_thresholds(n: int):
+    """Largest ||G||_2 of each scheme in a propagation of n slices: the Taylor
+    remainder theta^(m+1)/(m+1)! / (1 - theta/(m+2)) at max(2^-60, 2^-53 / (8 sqrt n))."""
+    import math
+    u = max(2.0 ** -60, 2.0 ** -53 / (8.0 * math.sqrt(n)))
+    out = []
+    for m in SCHEME_DEGREES:
+        lo, hi = 0.0, m + 1.0
+        for _ in range(200):
+            x = 0.5 * (lo + hi)
+            if x ** (m + 1) / math.factorial(m + 1) / (1.0 - x / (m + 2)) <= u:
+                lo = x
+            else:
+                hi = x
+        out.append(lo)
+    return out
+
+
+def norm2_bound(A) -> float:
+    """The engines' bound of ||A||_2: (||A^n||_F)^(1/n), n = 16 (8 above 32 levels)."""
+    squarings = 4 if A.shape[0] <= 32 else 3
+    n1 = float(np.max(np.sum(np.abs(A), axis=0)))
+    if n1 == 0.0:
+        return 0.0
+    X, lg = A / n1, 0.0
+    for _ in range(squarings):
+        X = X @ X
+        f = float(np.linalg.norm(X))
+        lg = 2.0 * lg + np.log(f)
+        X = X / f
+    return min(n1, n1 * float(np.exp(lg / 2 ** squarings)))
+
+
+def scheme_products(bound: float, nu: float, th) -> int:
+    """Products and squarings of a slice with that bound of ||G||_2 and ||G||_1 = nu."""
+    for q, t in enumerate(th):
+        if bound <= t:
+            return q
+    x = min(bound, nu)
+    return min(q + max(0, int(np.ceil(np.log2(x / t)))) for q, t in enumerate(th))
 
 
 def engine_dim(d: int) -> int:
@@ -75,11 +112,11 @@ def engine_dim(d: int) -> int:
 
 def algorithmic_flops(pm, w, precision, n_leaves: int) -> float:
     """Flops the kernel's algorithm needs for one propagation: per slice
-    8 d^3 per complex product over the series' products (series_products),
-    the s squarings and the chain product, plus 4 M d^2 for the expand; the
-    tree adds (n_leaves - 1) products.  (m, s) per slice come from the
-    library's planner on ||G_j||_1 (FP64 above dimension 4: an upper bound, the
-    engines plan by a bound of the 2-norm)."""
+    8 d^3 per complex product over the series' products, the squarings and
+    the chain product, plus 4 M d^2 for the expand; the tree adds
+    (n_leaves - 1) products.  Per slice: FP64 above dimension 4 the scheme that
+    the engines pick by their bound of ||G_j||_2 (scheme_products), otherwise
+    the library planner's (m, s) on ||G_j||_1."""
     D = engine_dim(w.dim)
     B, _ = pm.build_basis_host(w.H0, w.Hk, w.order)
     M = B.shape[0]
@@ -102,12 +139,21 @@ def algorithmic_flops(pm, w, precision, n_leaves: int) -> float:
                 Wt[:, q] = (h * h / 12) * (s0[a] * s2[b] - s2[a] * s0[b])
                 q += 1
     prods = 0
+    tiles = precision == 0 and w.dim > 4
+    if tiles:
+        th = scheme_thresholds(n)
+        beta = np.array([norm2_bound(A) if m <= K else float(np.max(np.sum(np.abs(A), axis=0)))
+                         for m, A in enumerate(B)])
+        bounds = np.abs(Wt) @ beta
     for c0 in range(0, n, 8192):
         G = np.tensordot(Wt[c0:c0 + 8192], B, axes=1)
         nu = np.max(np.sum(np.abs(G), axis=1), axis=1)
-        for x in nu:
-            m, s = pm.plan_expm(float(x), precision, n_slices=n)
-            prods += series_products(m, precision, w.dim) + s + 1
+        for i, x in enumerate(nu):
+            if tiles:
+                prods += scheme_products(bounds[c0 + i], float(x), th) + 1
+            else:
+                m, s = pm.plan_expm(float(x), precision, n_slices=n)
+                prods += taylor_products(m) + s + 1
     prods += n_leaves - 1
     return 8.0 * D ** 3 * prods + 4.0 * M * D * D * n
 
