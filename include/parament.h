@@ -334,11 +334,11 @@ pm_status pm_set_chunk(pm_ctx *ctx, int64_t chunk);
  * arbitration and would otherwise finish early, leaving the second ones to
  * run alone.  percent in [0, 100] (0: equal chains), -1 (default) the
  * automatic choice: 25 in PM_FP64; in the other precisions 20 for dimensions
- * 5..16 (and slice pairs of dimension <= 8), 0 for dimensions <= 4.  Chains
- * of dimensions <= 4 stay whole multiples of 1024 slices.  U(T) changes only
- * by the association of the chain products (rounding).  Not applied to the
- * gradient's or the trajectory's forward pass.  PM_E_INVALID_ARG outside
- * that range. */
+ * 5..16 (and slice pairs of dimension <= 8), 0 for dimensions <= 4.  Uneven
+ * chains of dimensions <= 4 are whole multiples of 1024 slices (equal ones can
+ * be as short as 64).  U(T) changes only by the association of the chain
+ * products (rounding).  Not applied to the gradient's or the trajectory's
+ * forward pass.  PM_E_INVALID_ARG outside that range. */
 pm_status pm_set_chain_skew(pm_ctx *ctx, int percent);
 
 /* ---- device workspace ---------------------------------------------------
