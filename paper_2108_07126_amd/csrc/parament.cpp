@@ -1311,12 +1311,12 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
     if (!g.ok) return hip_fail(ctx, hipErrorInvalidDevice, "hipSetDevice");
     hipError_t he = hipDeviceSynchronize();
     if (he != hipSuccess) return hip_fail(ctx, he, "hipDeviceSynchronize");
+    ctx->ready = false;   // until the new basis is whole: any error below leaves none
     dfree(ctx->d_basis);
     he = hipMalloc((void**)&ctx->d_basis, lay.size() * sizeof(double));
     if (he != hipSuccess) {
         ctx->d_basis = nullptr;
         (void)hipGetLastError();
-        ctx->ready = false;
         return fail(ctx, PM_E_OOM, "hipMalloc failed for the basis");
     }
     he = hipMemcpy(ctx->d_basis, lay.data(), lay.size() * sizeof(double), hipMemcpyHostToDevice);
@@ -1334,7 +1334,6 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
             if (he != hipSuccess) {
                 ctx->d_basis_grad = nullptr;
                 (void)hipGetLastError();
-                ctx->ready = false;
                 return fail(ctx, PM_E_OOM, "hipMalloc failed for the gradient basis");
             }
             he = hipMemcpy(ctx->d_basis_grad, glay.data(), glay.size() * sizeof(double), hipMemcpyHostToDevice);
@@ -1366,7 +1365,6 @@ pm_status pm_set_hamiltonian(pm_ctx* ctx, int64_t dim, const double* H0, int64_t
         if (he != hipSuccess) {
             ctx->d_basis_pair = nullptr;
             (void)hipGetLastError();
-            ctx->ready = false;
             return fail(ctx, PM_E_OOM, "hipMalloc failed for the slice-pair basis");
         }
         he = hipMemcpy(ctx->d_basis_pair, play.data(), play.size() * sizeof(double), hipMemcpyHostToDevice);
